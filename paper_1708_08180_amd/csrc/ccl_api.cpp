@@ -141,7 +141,6 @@ ImgView make_view(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, uint3
     v.tilesX = (W + kTileW - 1) / kTileW;
     v.tilesY = (H + th - 1) / th;
     v.n = (uint32_t)((uint64_t)H * (uint64_t)W);
-    v.aligned16 = (((uintptr_t)img & 15u) == 0 && (pitch & 15) == 0) ? 1 : 0;
     return v;
 }
 

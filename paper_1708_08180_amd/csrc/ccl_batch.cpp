@@ -296,9 +296,7 @@ int ccl_label_batch(ccl_ctx *ctx, const ccl_image_desc *descs, int32_t n, int32_
         b.tilesX = (d.W + kTileW - 1) / kTileW;
         b.tilesY = (d.H + th - 1) / th;
         b.n = (uint32_t)((uint64_t)d.H * (uint64_t)d.W);
-        b.aligned16 = (((uintptr_t)d.img & 15u) == 0 && (d.pitch & 15) == 0) ? 1 : 0;
         b.tile_base = tb;
-        b.pad = 0;
         htb[i] = tb;
         if ((i & 63) == 0) hcb[i >> 6] = tb;
         tb += (uint32_t)b.tilesX * (uint32_t)b.tilesY;

@@ -483,7 +483,6 @@ __device__ __forceinline__ ImgView batch_view(const BatchImage &b, const BatchWs
     v.tilesX = b.tilesX;
     v.tilesY = b.tilesY;
     v.n = b.n;
-    v.aligned16 = b.aligned16;
     return v;
 }
 

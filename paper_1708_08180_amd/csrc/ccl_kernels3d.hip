@@ -37,20 +37,11 @@ struct Vol {
     int32_t D, H, W;
     int32_t tilesX, tilesY, tilesZ;
     uint32_t n;
-    int32_t aligned16;
 };
 
 __device__ __forceinline__ uint4 load_chunk3d(const Vol &v, int x0, int y, int z, int q) {
-    uint4 b = make_uint4(0u, 0u, 0u, 0u);
-    if (y >= v.H || z >= v.D) return b;
-    const int x = x0 + q * 16;
-    const uint8_t *p = v.vol + (int64_t)z * v.pitch_z + (int64_t)y * v.pitch_y + x;
-    if (v.aligned16 && x + 16 <= v.W) return *(const uint4 *)p;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        if (x + i < v.W) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
-    return make_uint4(w[0], w[1], w[2], w[3]);
+    if (y >= v.H || z >= v.D) return make_uint4(0u, 0u, 0u, 0u);
+    return load_row16(v.vol + (int64_t)z * v.pitch_z + (int64_t)y * v.pitch_y, x0 + q * 16, v.W);
 }
 
 __device__ __forceinline__ void tile_of(const Vol &v, uint32_t t, int &tx, int &ty, int &tz) {
@@ -302,7 +293,6 @@ extern "C" int ccl_label_3d(const uint8_t *vol, int32_t D, int32_t H, int32_t W,
     v.tilesY = (H + kTY - 1) / kTY;
     v.tilesZ = (D + kTZ - 1) / kTZ;
     v.n = (uint32_t)n;
-    v.aligned16 = (((uintptr_t)vol & 15u) == 0 && (pitch_y & 15) == 0 && (pitch_z & 15) == 0) ? 1 : 0;
     const uint64_t tiles = (uint64_t)v.tilesX * v.tilesY * v.tilesZ;
     if (tiles * kRows > 0x7FFFFFFFull) return CCL_ERR_TOO_LARGE;
     hipStream_t s = (hipStream_t)stream;
