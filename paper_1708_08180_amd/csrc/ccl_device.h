@@ -151,18 +151,7 @@ __device__ __forceinline__ uint32_t batch_image_of(const BatchArgs &a, uint32_t 
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
-// Smallest s <= j such that bits s..j of m are all set (bit j must be set).
-__device__ __forceinline__ int run_start(uint64_t m, int j) {
-    const uint64_t below = ~m & ((2ull << j) - 1ull);  // j == 63 wraps to all ones
-    return below ? 64 - __clzll((long long)below) : 0;
-}
-
 __device__ __forceinline__ int bit(uint64_t m, int j) { return (int)((m >> j) & 1ull); }
-
-// Foreground cell j of row mask m that begins a run.
-__device__ __forceinline__ bool is_run_start(uint64_t m, int j) {
-    return bit(m, j) && !(j > 0 && bit(m, j - 1));
-}
 
 template <typename T>
 __device__ __forceinline__ T lds_ld(const T *p) {
@@ -406,11 +395,13 @@ __device__ __forceinline__ uint4 load_row16(const uint8_t *row, int x, int W) {
         const uint64_t hi = sh < 64 ? h[1] >> sh : 0ull;
         return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
     }
-    uint32_t w[4] = {0u, 0u, 0u, 0u};  // W < 16: the row's only chunk (x == 0)
-#pragma unroll
-    for (int i = 0; i < 15; ++i)
-        if (x + i < W) w[i >> 2] |= (uint32_t)row[x + i] << (8 * (i & 3));
-    return make_uint4(w[0], w[1], w[2], w[3]);
+    uint64_t lo = 0ull, hi = 0ull;  // W < 16: the row's only chunk (x == 0)
+#pragma unroll 1
+    for (int i = W - 1; i >= 0; --i) {
+        hi = (hi << 8) | (lo >> 56);
+        lo = (lo << 8) | row[i];
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
 // 16 pixels of one tile row: row `row` of tile (tx, ty), columns
@@ -521,71 +512,41 @@ __device__ __forceinline__ PairMasks pair_masks(uint64_t d, uint64_t u, uint64_t
     return p;
 }
 
-// Sweep of one wavefront's band of rows, top to bottom (Sec. II-A-2/3).
-// `ra` carries, per lane, the root node of the pixel above (kNone for
-// background), so the roots a run touches come from neighbouring lanes'
-// registers.  A run's parent becomes the smallest of those roots (one LDS
-// atomicMin per lane on its node).  Every other root it touches is then
-// linked under that one; they were roots when the row began, so one
-// atomicMin per link normally does it, and only a link that finds its root
-// already linked elsewhere in this row continues as a walk up both trees.  After
-// a row with links the row's roots are re-resolved, so `ra` always holds
-// true roots.
-//
-// Node numbering: the first node of tile row j is lane j's value of `rbv`
-// (a row's nodes are consecutive and rows follow each other, so nodes stay
-// in raster order of run starts): either dense, an exclusive scan of the
-// rows' run counts, or sparse, j * 32.  A foreground cell's run follows the
-// runs that end before it.  cr[node] = first column | row << 8.
-template <int TH, int RPW, bool CONN8>
-__device__ __forceinline__ void sweep_band(uint32_t *par, uint16_t *cr, const uint64_t *msk,
-                                           int wave, int lane, uint32_t rbv) {
-    uint32_t ra = kNone;
-    uint64_t u = 0;
-    uint64_t m[RPW];
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) m[k] = uniform64(msk[wave * RPW + k]);
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-        const int r = wave * RPW + k;
-        const uint64_t d = m[k];
-        const uint64_t S = run_starts(d);
-        const bool fg = lane_in(d), isS = lane_in(S);
-        const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)rbv, r);
-        const uint32_t node = bits_below_plus(run_ends(d), rb);
-        uint32_t *pn = &par[node];
-        if (isS) {
-            lds_st(pn, node);
-            cr[node] = (uint16_t)(lane | (r << 8));
-        }
-        uint32_t md = fg ? node : kNone;
-        if (k > 0) {
-            const PairMasks p = pair_masks<CONN8>(d, u);
-            const uint32_t rL = from_left(ra, kNone), rR = from_right(ra, kNone);
-            // PL and PM are disjoint
-            const uint32_t t0 = lane_in(p.pm) ? ra : (lane_in(p.pl) ? rL : kNone);
-            const uint32_t t1 = lane_in(p.pr) ? rR : kNone;
-            const uint32_t tm = t0 < t1 ? t0 : t1;
-            if (tm != kNone) atomicMin(pn, tm);
-            if (fg) md = lds_ld(pn);  // the smallest root the run touches
-            const bool n0 = t0 != kNone && t0 != md;
-            const bool n1 = t1 != kNone && t1 != md;
-            if (__ballot(n0 || n1)) {
-                uint32_t o0 = 0, o1 = 0;
-                if (n0) o0 = atomicMin(&par[t0], md);
-                if (n1) o1 = atomicMin(&par[t1], md);
-                const bool r0 = n0 && o0 < t0 && o0 != md, r1 = n1 && o1 < t1 && o1 != md;
-                if (__ballot(r0 || r1)) {
-                    if (r0) lds_link(par, md, o0);
-                    if (r1) lds_link(par, md, o1);
-                }
-                if (fg) md = lds_root(par, md);
-                if (isS) lds_st(pn, md);
-            }
-        }
-        ra = md;
-        u = d;
-    }
+// Which intervals of a lower line touch which intervals of an upper line,
+// as one request per touching pair.  Inputs, bit j = column j:
+//   st / l / r   the lower line's column j touches the upper line's column
+//                j / j - 1 / j + 1;
+//   M, S, E      the lower line's columns, and the first and last columns of
+//                its intervals (maximal segments; two of them may be adjacent);
+//   Mu, Su, Eu   the same of the upper line.
+// Result: f has one column per pair of intervals that share a column and
+// touch (anywhere): the pair is the two intervals of that column.  l / r have
+// the columns j where the lower interval that starts / ends at j touches the
+// upper interval that ends at j - 1 / starts at j + 1 and shares no column
+// with it.
+struct PairRequests { uint64_t f, l, r; };
+
+__host__ __device__ __forceinline__ PairRequests pair_requests(uint64_t st, uint64_t l, uint64_t r, uint64_t M,
+                                                               uint64_t S, uint64_t E, uint64_t Mu, uint64_t Su,
+                                                               uint64_t Eu) {
+    // a diagonal touch of two intervals that share a column is a touch at
+    // such a column: at j when the upper interval goes on to j, at the
+    // neighbouring column when the lower interval goes on to it
+    const uint64_t upl = Mu & ~Su;         // the upper intervals of j - 1 and j are one
+    const uint64_t upr = Mu & ~(Su >> 1);  // those of j and j + 1 are one (where j + 1 is in one)
+    const uint64_t c = st | (l & upl) | ((l & ~S) >> 1) | (r & upr) | ((r & ~E) << 1);
+    // first touching column of every segment of columns shared by one pair:
+    // adding the segments' first columns to their untouched columns carries
+    // through those up to the first touching one (a carry never leaves its
+    // segment, whose last column is left clear)
+    const uint64_t D = M & Mu;
+    const uint64_t Sb = D & (~(D << 1) | S | Su);
+    const uint64_t Eb = D & (~(D >> 1) | E | Eu);
+    PairRequests q;
+    q.f = ((D & ~c & ~Eb) + Sb) & c;
+    q.l = l & S & ~upl;
+    q.r = r & E & ~upr;
+    return q;
 }
 
 // ------------------------------------------------- two-row band nodes
@@ -655,8 +616,8 @@ __device__ __forceinline__ void key_link(uint32_t *par, uint32_t a, uint32_t b) 
     }
 }
 
-// Sweep of one wavefront's bands, top to bottom, as sweep_band does for
-// rows: `ra` carries per lane the root key of the interval holding the
+// Sweep of one wavefront's bands, top to bottom (Sec. II-A-2/3): `ra`
+// carries per lane the root key of the interval holding the
 // pixel above the band's top row (kNone for background); a band's
 // interval takes the smallest root its top row touches (one LDS atomicMin
 // per lane on its node), every other touched root is linked under it, and
