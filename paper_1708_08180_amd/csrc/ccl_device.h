@@ -6,11 +6,9 @@
 // (w+1)*RPW) with RPW = TH / NW.  A tile row is a 64-bit foreground mask, so
 // the paper's row scan plus row-column unification (Sec. II-A-2) collapses
 // to mask arithmetic: binary labeling takes two rows at a time, and the
-// components of such a band are column intervals found from its two masks
-// (see sweep_bands); those intervals are the union-find nodes.  The local
-// UF (Sec. II-A-3) then merges each interval with the intervals of the band
-// above that it touches through LDS atomicMin, always linking the node with
-// the larger smallest pixel under the other.  Equal-value labeling keeps one
+// components of such a band are column intervals found from its two masks;
+// those intervals are the union-find nodes, joined with the intervals of the
+// band above that they touch (LineForest).  Equal-value labeling keeps one
 // node per run of equal values in a row.
 //
 // Forest encoding in global memory.  labels[p] holds 1 + parent(p); a root r
@@ -413,13 +411,7 @@ __device__ __forceinline__ uint4 load_chunk(const V &v, int tx, int ty, int th, 
     return load_row16(v.img + (int64_t)y * v.pitch, tx * kTileW + q * 16, v.W);
 }
 
-// ------------------------------------------------- run-indexed local forest
-//
-// Inside K1 the union-find nodes are runs: run k (0-based, left to right) of
-// tile row r is node r*32 + k.  Run order within a row follows the columns
-// and rows follow each other, so node order is raster order of run starts
-// and the smallest node of a component is the run holding its smallest
-// pixel.  col[node] keeps the run's first column.
+// ------------------------------------------------------ masks and lanes
 
 // Lane predicate from a wave-uniform 64-bit mask (no VALU work).
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
@@ -561,27 +553,8 @@ __host__ __device__ __forceinline__ PairRequests pair_requests(uint64_t st, uint
 // and over half as many steps as rows.
 //
 // Node n of a tile is its n-th interval in band order, left to right inside
-// a band.  Every parent entry holds a key, the node's smallest pixel (tile
-// row << 6 | column) above its node's byte offset in the parent array
-// (node << 2, so a key addresses its entry with one mask): an atomicMin on
-// keys links the tree whose node holds the larger pixel under the other, so
-// the root of every tree is the node holding the component's smallest pixel
-// (the linking rule of Sec. II-A-3, with pixels as the order).  A root's
-// entry is its own key.
-
-constexpr uint32_t kNodeBits = 14;  // the byte offsets of at most 4096 nodes per tile (64 intervals per band)
-constexpr uint32_t kNodeMask = ((1u << 12) - 1u) << 2;
-
-// Key of node n whose smallest pixel is pos.
-__device__ __forceinline__ uint32_t node_key(uint32_t pos, uint32_t n) { return (pos << kNodeBits) | (n << 2); }
-
-// Parent entry of the node that key k names.
-__device__ __forceinline__ uint32_t *key_entry(uint32_t *par, uint32_t k) {
-    return (uint32_t *)((char *)par + (k & kNodeMask));
-}
-__device__ __forceinline__ const uint32_t *key_entry(const uint32_t *par, uint32_t k) {
-    return (const uint32_t *)((const char *)par + (k & kNodeMask));
-}
+// a band, so a component's root, its smallest node, lies in the component's
+// first band.
 
 // First column of every interval of the band (t above b).
 template <bool CONN8>
@@ -596,125 +569,90 @@ __device__ __forceinline__ uint64_t band_starts(uint64_t t, uint64_t b) {
 // interval starts s.
 __device__ __forceinline__ uint64_t band_ends(uint64_t m, uint64_t s) { return m & (~(m >> 1) | (s >> 1)); }
 
-// Root key of the tree holding key k (read-only walk; see lds_root).
-__device__ __forceinline__ uint32_t key_root(const uint32_t *par, uint32_t k) {
+// Local union-find over the intervals of a tile's lines (two-row bands, or
+// rows in equal-value labeling), whose nodes are numbered densely line by
+// line.  Nothing in it follows the lines one after the other: every touching
+// pair of intervals of neighbouring lines is known beforehand
+// (pair_requests), and each thread takes the pairs of eight columns of a
+// line.
+//   hooks      a pair is one LDS atomicMin that hooks the lower interval
+//              under the upper one; where it was hooked before, the two upper
+//              intervals are listed as a join
+//   compress   every node is pointed at the root of its tree of hooks
+//   joins      the listed pairs, between roots or next to them
+//   compress   every node is pointed at its root
+// (Sec. II-A-3 with the larger node under the smaller.)  Hooks alone build
+// trees as deep as the tile has lines; joining along them without the
+// compression in between would walk them again and again.
+// The local merge is bound by instruction issue and by the chain of LDS round
+// trips between its barriers.  A wavefront that swept its bands one after the
+// other, carrying each column's root in a register, issued more instructions
+// in one long chain; local merge, both on one card: 4096 x 4096 p = 0.5,
+// 8-connectivity 28.0 us with the sweep, 22.4 so; 8192 x 8192 smoothed 63 and
+// 47; serpentine 56 and 32; 3001 x 4099 4-connectivity 18.6 and 15.6.
+template <int LINES, int NODES, int JOINS>
+struct LineForest {
+    uint32_t par[NODES];
+    uint32_t join[JOINS];      // upper nodes of a join, 16 bits each
+    uint16_t info[NODES];      // line << 6 | first column of the interval
+    uint64_t E[LINES];         // interval ends
+    uint64_t f[LINES], l[LINES], r[LINES];  // touching pairs with the line above
+    uint16_t base[LINES];      // first node of the line
+    uint16_t pre[LINES * 8];   // first node at or after every eighth column
+    uint32_t joins;
+};
+
+// First node at or after column 8 q of line k, and the nodes of its eight
+// columns' intervals, given the interval starts S.
+template <class F>
+__device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S) {
+    const uint64_t E = sh.E[k];
+    const uint32_t e8 = (uint32_t)(E >> (8 * q)) & 0xFFu;
+    const uint32_t first = (uint32_t)sh.base[k] + (uint32_t)__popcll(E & ((1ull << (8 * q)) - 1ull));
+    sh.pre[k * 8 + q] = (uint16_t)first;
+    for (uint32_t s8 = (uint32_t)(S >> (8 * q)) & 0xFFu; s8; s8 &= s8 - 1u) {
+        const uint32_t b = (uint32_t)__builtin_ctz(s8);
+        const uint32_t n = first + (uint32_t)__builtin_popcount(e8 & ((1u << b) - 1u));
+        sh.info[n] = (uint16_t)(((uint32_t)k << 6) | ((uint32_t)q << 3) | b);
+        lds_st(&sh.par[n], n);
+    }
+}
+
+// Hooks of columns [8 q, 8 q + 8) of line k >= 1.
+template <bool DIAG, int LINES, int NODES, int JOINS>
+__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS> &sh, int k, int q) {
+    const int i = k * 8 + q;
+    uint32_t m = ((const uint8_t *)sh.f)[i];
+    if (DIAG) m |= ((uint32_t)((const uint8_t *)sh.l)[i] << 8) | ((uint32_t)((const uint8_t *)sh.r)[i] << 16);
+    const uint32_t e8 = ((const uint8_t *)sh.E)[i], u8 = ((const uint8_t *)sh.E)[i - 8];
+    const uint32_t first = sh.pre[i], ufirst = sh.pre[i - 8];
+    for (; m; m &= m - 1u) {
+        const uint32_t p = (uint32_t)__builtin_ctz(m), b = p & 7u, below = (1u << b) - 1u;
+        const uint32_t lo = first + (uint32_t)__builtin_popcount(e8 & below);
+        uint32_t up = ufirst + (uint32_t)__builtin_popcount(u8 & below);
+        if (DIAG) {
+            if (p >= 16u) up += (u8 >> b) & 1u;  // the interval that starts right of b
+            else if (p >= 8u) up -= 1u;          // the one that ends left of b
+        }
+        const uint32_t old = atomicMin(&sh.par[lo], up);
+        if (old != lo && old != up) {
+            const uint32_t j = atomicAdd(&sh.joins, 1u);
+            if (j < (uint32_t)JOINS) sh.join[j] = old | (up << 16);
+            else lds_link(sh.par, old, up);
+        }
+    }
+}
+
+// Root of node n, whose owner alone stores to it, always an ancestor.  Stops
+// on any entry that is no smaller than its node.
+__device__ __forceinline__ uint32_t compress_node(uint32_t *par, uint32_t n) {
+    uint32_t p = lds_ld(&par[n]);
+    if (p >= n) return n;
     while (true) {
-        const uint32_t p = lds_ld(key_entry(par, k));
-        if (p >= k) return k;
-        k = p;
-    }
-}
-
-// Join the trees of the nodes with keys a and b (or of any of their
-// ancestors), as lds_link does with node numbers.
-__device__ __forceinline__ void key_link(uint32_t *par, uint32_t a, uint32_t b) {
-    while (a != b) {
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(key_entry(par, b), a);
-        if (old >= b) return;
-        b = old;
-    }
-}
-
-// Sweep of one wavefront's bands, top to bottom (Sec. II-A-2/3): `ra`
-// carries per lane the root key of the interval holding the
-// pixel above the band's top row (kNone for background); a band's
-// interval takes the smallest root its top row touches (one LDS atomicMin
-// per lane on its node), every other touched root is linked under it, and
-// the bottom row's pixels hand the interval's root on to the next band.
-// The first node of band j is lane j's value of `bbv`; ends[j] holds the
-// band's interval ends.  Touching pairs come from pair_masks over the top
-// row and the row above; several of them may name the same two intervals.
-template <int BPW, bool CONN8>
-__device__ __forceinline__ void sweep_bands(uint32_t *par, const uint64_t *msk, const uint64_t *ends,
-                                            int wave, int lane, uint32_t bbv) {
-    uint32_t ra = kNone;
-    uint64_t u = 0;
-    uint64_t m[2 * BPW], e[BPW];
-#pragma unroll
-    for (int k = 0; k < 2 * BPW; ++k) m[k] = uniform64(msk[wave * 2 * BPW + k]);
-#pragma unroll
-    for (int k = 0; k < BPW; ++k) e[k] = uniform64(ends[wave * BPW + k]);
-#pragma unroll
-    for (int k = 0; k < BPW; ++k) {
-        const int band = wave * BPW + k;
-        const uint64_t t = m[2 * k], b = m[2 * k + 1];
-        const uint64_t M = t | b, E = e[k];
-        const uint64_t S = band_starts<CONN8>(t, b);
-        const bool in = lane_in(M);
-        const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)bbv, band);
-        const uint32_t node = bits_below_plus(E, rb);
-        uint32_t *pn = &par[node];
-        if (lane_in(S)) {
-            // the interval's smallest pixel: its first top-row pixel, else
-            // its first pixel (a bottom-row one, at the start column).  Seen
-            // from the start column, the first top-row pixel belongs to the
-            // interval when it comes no later than the interval's end (the
-            // first end at or after the start, so er != 0)
-            const uint64_t tr = t >> lane, er = E >> lane;
-            const uint32_t dt = tr ? (uint32_t)__builtin_ctzll(tr) : 64u;
-            const bool top = dt <= (uint32_t)__builtin_ctzll(er);
-            const uint32_t row = (uint32_t)(2 * band) + (top ? 0u : 1u);
-            const uint32_t col = (uint32_t)lane + (top ? dt : 0u);
-            lds_st(pn, node_key((row << 6) | col, node));
-        }
-        uint32_t md = kNone;
-        if (k > 0) {
-            const PairMasks p = pair_masks<CONN8>(t, u);
-            // PL never holds lane 0 and PR never lane 63 (no column beyond the tile)
-            const uint32_t rL = from_left_any(ra), rR = from_right_any(ra);
-            const uint32_t t0 = lane_in(p.pm) ? ra : (lane_in(p.pl) ? rL : kNone);
-            const uint32_t t1 = lane_in(p.pr) ? rR : kNone;
-            const uint32_t tm = t0 < t1 ? t0 : t1;
-            if (tm != kNone) atomicMin(pn, tm);
-            if (in) md = lds_ld(pn);
-            const bool n0 = t0 != kNone && t0 != md;
-            const bool n1 = t1 != kNone && t1 != md;
-            if (__ballot(n0 || n1)) {
-                uint32_t o0 = 0, o1 = 0;
-                if (n0) o0 = atomicMin(key_entry(par, t0), md);
-                if (n1) o1 = atomicMin(key_entry(par, t1), md);
-                const bool r0 = n0 && o0 < t0 && o0 != md, r1 = n1 && o1 < t1 && o1 != md;
-                if (__ballot(r0 || r1)) {
-                    if (r0) key_link(par, md, o0);
-                    if (r1) key_link(par, md, o1);
-                }
-                // under 8-connectivity the walk to the current root pays:
-                // dense images link many roots per band, and carrying a
-                // root that was just linked elsewhere deepens the trees the
-                // next bands walk; under 4-connectivity it does not pay
-                // (measured), and key_link tolerates a stale root
-                if (CONN8) {
-                    if (in) md = key_root(par, md);
-                    if (lane_in(S)) lds_st(pn, md);
-                }
-            }
-        } else if (in) {
-            md = lds_ld(pn);
-        }
-        ra = lane_in(b) ? md : kNone;
-        u = b;
-    }
-}
-
-// Band seam of a multi-wavefront tile: the top row of band k against the
-// bottom row of band k - 1, any forest state.  bk / bu: first node of band
-// k / k - 1.
-template <bool CONN8>
-__device__ __forceinline__ void merge_band_seam(uint32_t *par, const uint64_t *msk, const uint64_t *ends,
-                                                int k, uint32_t bk, uint32_t bu) {
-    const uint64_t t = uniform64(msk[2 * k]), u = uniform64(msk[2 * k - 1]);
-    const uint64_t E = uniform64(ends[k]), Eu = uniform64(ends[k - 1]);
-    const uint32_t node = bk + bits_below(E);
-    const uint32_t upC = bu + bits_below(Eu);  // interval of the upper cell in this column
-    auto join = [&](uint32_t a, uint32_t b) { key_link(par, lds_ld(&par[a]), lds_ld(&par[b])); };
-    const PairMasks p = pair_masks<CONN8>(t, u);
-    if (CONN8) {
-        if (lane_in(p.pl)) join(node, bu + bits_below(Eu << 1));
-        else if (lane_in(p.pm)) join(node, upC);
-        if (lane_in(p.pr)) join(node, upC + (uint32_t)bit(Eu, (int)(threadIdx.x & 63)));
-    } else {
-        if (lane_in(p.pm)) join(node, upC);
+        const uint32_t g = lds_ld(&par[p]);
+        if (g >= p) return p;
+        p = g;
+        lds_st(&par[n], p);
     }
 }
 

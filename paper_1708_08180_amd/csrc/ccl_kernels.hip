@@ -152,14 +152,15 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
     __syncthreads();  // LDS may be reused for another tile
 }
 
-// Binary local merge over two-row bands (see sweep_bands).
-template <int TH>
+// Binary local merge over two-row bands.
+template <int TH, bool CONN8>
 struct K1BandLds {
-    uint32_t par[TH * kSlotsPerRow];  // node keys (a band has at most 64 intervals)
-    uint64_t msk[TH];                 // per row: foreground mask
-    uint64_t ends[TH / 2];            // per band: interval ends
-    uint64_t flg[TH];                 // per row: local roots of edge-touching components
-    uint16_t bbase[TH / 2];           // first node of every band
+    static constexpr int NB = TH / 2;
+    static constexpr int NODES = NB * (CONN8 ? 32 : 64);  // a band's most intervals
+    LineForest<NB, NODES, 16 * TH> f;
+    uint64_t msk[TH];  // per row: foreground mask
+    uint64_t flg[TH];  // per row: local roots of edge-touching components
+    uint32_t nodes;
 };
 
 // Kernel 1 body for tile t of image v, binary labeling.  Writes the tile's
@@ -168,15 +169,13 @@ struct K1BandLds {
 // of the edge cells, and seeds those roots in the forest.  Ends after a
 // workgroup barrier.
 template <int TH, int NW, bool CONN8>
-__device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1BandLds<TH> &sh) {
-    constexpr int RPW = TH / NW;
-    static_assert(RPW % 2 == 0, "a wavefront owns whole bands");
-    constexpr int BPW = RPW / 2;
+__device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1BandLds<TH, CONN8> &sh) {
     constexpr int NB = TH / 2;
     constexpr int NT = NW * 64;
     constexpr int CH = TH * 4;               // 16-byte chunks per tile
     constexpr int LPT = (CH + NT - 1) / NT;  // chunks per thread
-    uint32_t *par = sh.par;
+    auto &F = sh.f;
+    uint32_t *par = F.par;
     uint64_t *msk = sh.msk;
     uint64_t *flg = sh.flg;
     const int tid = (int)threadIdx.x, lane = tid & 63;
@@ -195,44 +194,97 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
     __syncthreads();
     // every band's intervals, one band per lane: nodes are numbered densely
     // (an exclusive scan of the bands' interval counts)
-    uint32_t bbv, nodes;
-    {
+    if (wave == 0) {
         const uint64_t bt = lane < NB ? msk[2 * lane] : 0ull, bb = lane < NB ? msk[2 * lane + 1] : 0ull;
         const uint64_t s = band_starts<CONN8>(bt, bb);
-        bbv = wave_exclusive_scan((uint32_t)__popcll(s), &nodes);
-        if (tid < NB) {
-            sh.ends[tid] = band_ends(bt | bb, s);
-            sh.bbase[tid] = (uint16_t)bbv;
+        uint32_t nodes;
+        const uint32_t b = wave_exclusive_scan((uint32_t)__popcll(s), &nodes);
+        if (lane < NB) {
+            F.E[lane] = band_ends(bt | bb, s);
+            F.base[lane] = (uint16_t)b;
+        }
+        if (lane == 0) {
+            sh.nodes = nodes;
+            F.joins = 0u;
         }
     }
     __syncthreads();
-    sweep_bands<BPW, CONN8>(par, msk, sh.ends, wave, lane, bbv);
-    if (NW > 1) {
+    // the touching pairs of every band with the band above, one band per
+    // lane (on a wavefront that did not scan)
+    if (wave == (NW > 1 ? 1 : 0) && lane < NB && lane > 0) {
+        const uint64_t t0 = msk[2 * lane], u = msk[2 * lane - 1];
+        const uint64_t M = t0 | msk[2 * lane + 1], Mu = u | msk[2 * lane - 2];
+        const uint64_t S = band_starts<CONN8>(t0, msk[2 * lane + 1]);
+        const uint64_t Su = band_starts<CONN8>(msk[2 * lane - 2], u);
+        const PairRequests q = pair_requests(t0 & u, CONN8 ? t0 & (u << 1) : 0ull, CONN8 ? t0 & (u >> 1) : 0ull, M, S,
+                                             F.E[lane], Mu, Su, F.E[lane - 1]);
+        F.f[lane] = q.f;
+        F.l[lane] = q.l;
+        F.r[lane] = q.r;
+    }
+    for (int i = tid; i < NB * 8; i += NT) {
+        const int k = i >> 3;
+        forest_nodes(F, k, i & 7, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]));
+    }
+    __syncthreads();
+    for (int i = tid; i < NB * 8; i += NT)
+        if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
+    __syncthreads();
+    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
+    if (joins) {  // workgroup-uniform
+        for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) compress_node(par, n);
         __syncthreads();
-        if (wave > 0) {
-            const int k = wave * BPW;
-            merge_band_seam<CONN8>(par, msk, sh.ends, k, (uint32_t)__builtin_amdgcn_readlane((int)bbv, k),
-                                   (uint32_t)__builtin_amdgcn_readlane((int)bbv, k - 1));
+        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
+            const uint32_t e = F.join[i];
+            lds_link(par, lds_ld(&par[e & 0xFFFFu]), lds_ld(&par[e >> 16]));
+        }
+        __syncthreads();
+    }
+    // an interval's smallest pixel: its first top-row pixel, else its first
+    // pixel (a bottom-row one, at the start column)
+    auto smallest = [&](uint32_t n) {
+        const uint32_t in = F.info[n], k = in >> 6, s = in & 63u;
+        const uint64_t tr = msk[2 * k] >> s, er = F.E[k] >> s;
+        const uint32_t dt = tr ? (uint32_t)__builtin_ctzll(tr) : 64u;
+        const bool top = dt <= (uint32_t)__builtin_ctzll(er);
+        return ((2u * k + (top ? 0u : 1u)) << 6) | (s + (top ? dt : 0u));
+    };
+    // every node finds its root; a root's entry becomes kPixel | its smallest
+    // pixel, which walks still take for a root's (it is no smaller than any
+    // node)
+    constexpr uint32_t kPixel = 0x80000000u;
+    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT)
+        if (compress_node(par, n) == n) lds_st(&par[n], kPixel | smallest(n));
+    __syncthreads();
+    // a root without a top-row pixel: the component's smallest pixel may be
+    // the top-row pixel of another of its intervals in the band (once one
+    // has been entered, only of one that starts before it)
+    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
+        const uint32_t r = lds_ld(&par[n]);
+        if (r >= kPixel) continue;
+        const uint32_t e = lds_ld(&par[r]), in = F.info[n];
+        if ((in ^ (uint32_t)F.info[r]) >> 6 == 0u && ((e & 64u) || (in & 63u) < (e & 63u))) {
+            const uint32_t p = kPixel | smallest(n);
+            if (p < e) atomicMin(&par[r], p);
         }
     }
     __syncthreads();
-
-    // node-parallel finish: every node finds its root (read-only walk) and
-    // its owner alone stores it, so par[n] is the root's key afterwards; the
-    // node's record (the root's tile-local pixel) goes out
+    // records: the smallest pixel of the node's component
     uint16_t *sl = v.slots + (size_t)t * TH * kSlotsPerRow;
     for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
-        const uint32_t e = lds_ld(&par[n]);
-        const uint32_t root = key_root(par, e);
-        if (root != e) lds_st(&par[n], root);
-        sl[n] = (uint16_t)(root >> kNodeBits);
+        uint32_t e = lds_ld(&par[n]);
+        if (e < kPixel) {
+            e = lds_ld(&par[e]);
+            lds_st(&par[n], e);
+        }
+        sl[n] = (uint16_t)e;
     }
     __syncthreads();
     uint64_t *rw = v.rowmask + (size_t)t * rowmask_words(TH);
     for (int r = tid; r < TH; r += NT) rw[r] = msk[r];
     if (tid < NB) {
-        rw[rowmask_ends(TH) + tid] = sh.ends[tid];
-        ((uint16_t *)(rw + rowmask_bases(TH)))[tid] = sh.bbase[tid];
+        rw[rowmask_ends(TH) + tid] = F.E[tid];
+        ((uint16_t *)(rw + rowmask_bases(TH)))[tid] = F.base[tid];
     }
     // edge masks and edge-cell roots for the boundary analysis; every such
     // root is seeded in the forest (lanes of one component store the same
@@ -244,7 +296,7 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
         uint32_t *rt = v.roots + (size_t)t * roots_per_tile(TH);
         const uint64_t mTop = uniform64(msk[0]), mBot = uniform64(msk[TH - 1]);
         auto root_g = [&](uint32_t n) {
-            const uint32_t pos = lds_ld(&par[n]) >> kNodeBits;
+            const uint32_t pos = lds_ld(&par[n]) & (kPixel - 1u);
             atomicOr((unsigned long long *)&flg[pos >> 6], 1ull << (pos & 63u));
             return global_index(v, tx, ty, TH, pos);
         };
@@ -252,18 +304,16 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
             *dst = g;
             v.labels[g] = g + 1u;
         };
-        // first node of the last band, read while every lane is active (a
-        // lane that is off inside the branch below may not hold it)
-        const uint32_t bbLast = (uint32_t)__builtin_amdgcn_readlane((int)bbv, NB - 1);
+        const uint32_t bbLast = (uint32_t)F.base[NB - 1];
         if (wave == 0) {
-            if (hasUp && lane_in(mTop)) put(&rt[roots_top(TH) + lane], root_g(bits_below(uniform64(sh.ends[0]))));
+            if (hasUp && lane_in(mTop)) put(&rt[roots_top(TH) + lane], root_g(bits_below(uniform64(F.E[0]))));
             if (lane == 0) {
                 mk[kMaskTop] = mTop;
                 mk[kMaskBottom] = mBot;
             }
         }
         if (wave == 1 % NW && hasDown && lane_in(mBot))
-            put(&rt[roots_bottom(TH) + lane], root_g(bbLast + bits_below(uniform64(sh.ends[NB - 1]))));
+            put(&rt[roots_bottom(TH) + lane], root_g(bbLast + bits_below(uniform64(F.E[NB - 1]))));
         // per row (lane = row, 64 rows at a time): the band's first / last
         // interval holds the row's cell in the left / right column
         if (wave == 2 % NW || wave == 3 % NW) {
@@ -272,8 +322,8 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
                 const int r = 64 * h + lane;
                 const uint64_t mr = r < TH ? msk[r] : 0ull;
                 const bool lb = (mr & 1ull) != 0, rb = (mr >> 63) != 0;
-                const uint32_t bFirst = r < TH ? (uint32_t)sh.bbase[r >> 1] : 0u;
-                const uint32_t nInt = r < TH ? (uint32_t)__popcll(sh.ends[r >> 1]) : 0u;
+                const uint32_t bFirst = r < TH ? (uint32_t)F.base[r >> 1] : 0u;
+                const uint32_t nInt = r < TH ? (uint32_t)__popcll(F.E[r >> 1]) : 0u;
                 const uint64_t mLeft = __ballot(lb), mRight = __ballot(rb);
                 if (wave == 2 % NW) {
                     if (hasLeft && lb) put(&rt[roots_left(TH) + r], root_g(bFirst));
@@ -442,7 +492,7 @@ __global__ void __launch_bounds__(NW * 64) k1_local_merge(ImgView v) {
         __shared__ K1EqLds<TH> sh;
         k1_tile_eq<TH, NW, CONN8>(v, t, sh);
     } else {
-        __shared__ K1BandLds<TH> sh;
+        __shared__ K1BandLds<TH, CONN8> sh;
         k1_tile_bands<TH, NW, CONN8>(v, t, sh);
     }
 }
@@ -492,7 +542,7 @@ __device__ __forceinline__ ImgView batch_view(const BatchImage &b, const BatchWs
 // sizes the grids for every call.
 template <int TH, int NW, bool CONN8>
 __global__ void __launch_bounds__(NW * 64) k1_batch(BatchArgs a) {
-    __shared__ K1BandLds<TH> sh;
+    __shared__ K1BandLds<TH, CONN8> sh;
     const uint32_t g = xcd_remap(blockIdx.x, gridDim.x);
     if (g >= a.tiles) return;  // workgroup-uniform
     const uint32_t i = batch_image_of(a, g);
