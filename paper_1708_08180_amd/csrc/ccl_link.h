@@ -14,6 +14,8 @@
 // entry; output rows are full 256-byte lines.
 #pragma once
 
+#include <type_traits>
+
 #include "ccl_device.h"
 
 namespace ccl {
@@ -183,22 +185,37 @@ __device__ __forceinline__ void k3_write(const ImgView &v, const uint32_t *fin, 
     const uint32_t y0 = ty * (uint32_t)TH + (uint32_t)(wave * RPW);
     uint32_t *out = v.labels + origin + (uint32_t)(wave * RPW) * W + (uint32_t)lane;
     const bool full = (tx + 1u) * kTileW <= W && y0 + RPW <= (uint32_t)v.H;
-    // streaming stores: the output is not read again here, and keeping it
-    // out of the L2 leaves the records and the forest cached for the tiles
-    // still to run (a stale cached label is an ancestor)
+    // Streaming stores where every output row starts on a 128-byte line: the
+    // output is not read again here, and keeping it out of the L2 leaves the
+    // records and the forest cached for the tiles still to run (a stale cached
+    // label is an ancestor).  Elsewhere a line holds the pixels of two tiles,
+    // and streaming writes it to memory in two parts: ordinary stores let the
+    // L2 put them together.  Link of 4096 x 4096: 17.2 us streaming, 18.0
+    // ordinary; of 3001 x 4099: 20.4 streaming, 15.4 ordinary.
+    auto rows = [&](auto stream) {
+        auto store = [&](int k, uint32_t val) {
+            if (!(full || (x < W && y0 + k < (uint32_t)v.H))) return;
+            if (decltype(stream)::value) __builtin_nontemporal_store(val, &out[(size_t)k * W]);
+            else out[(size_t)k * W] = val;
+        };
 #pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        const uint32_t val = R.rec[i] != kNone ? fin[R.rec[i] & (TH * kTileW - 1)] + 1u : 0u;
-        if (EQ) {
-            if (full || (x < W && y0 + i < (uint32_t)v.H)) __builtin_nontemporal_store(val, &out[(size_t)i * W]);
-        } else {
-            const int k = 2 * i;
-            const uint32_t v0 = lane_in(R.m[k]) ? val : 0u, v1 = lane_in(R.m[k + 1]) ? val : 0u;
-            if (full || (x < W && y0 + k < (uint32_t)v.H)) __builtin_nontemporal_store(v0, &out[(size_t)k * W]);
-            if (full || (x < W && y0 + k + 1 < (uint32_t)v.H)) __builtin_nontemporal_store(v1, &out[(size_t)(k + 1) * W]);
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t val = R.rec[i] != kNone ? fin[R.rec[i] & (TH * kTileW - 1)] + 1u : 0u;
+            if (EQ) {
+                store(i, val);
+            } else {
+                store(2 * i, lane_in(R.m[2 * i]) ? val : 0u);
+                store(2 * i + 1, lane_in(R.m[2 * i + 1]) ? val : 0u);
+            }
         }
+    };
+    if ((W & 31u) == 0u && ((uintptr_t)v.labels & 127u) == 0u) {
+        rows(std::true_type{});
+        __syncthreads();
+    } else {
+        rows(std::false_type{});
+        __syncthreads();
     }
-    __syncthreads();
 }
 
 // The whole link for tile t.
