@@ -355,20 +355,19 @@ __device__ __forceinline__ uint32_t global_index(const ImgView &v, int tx, int t
     return (uint32_t)(y * (uint64_t)v.W + x);
 }
 
-// Bit i (i < 4) set iff byte i of w is nonzero: fold every byte onto its low
-// bit, then gather the four low bits into bits 28..31 with one multiply (the
-// shifted copies land on distinct bits below 24, so nothing carries).
-__device__ __forceinline__ uint32_t nonzero_bytes4(uint32_t w) {
-    uint32_t t = w | (w >> 4);
-    t |= t >> 2;
-    t |= t >> 1;
-    t &= 0x01010101u;
-    return (t * 0x10204080u) >> 28;
+// Top bit of every nonzero byte of w.
+__device__ __forceinline__ uint32_t nonzero_tops(uint32_t w) {
+    return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
 }
 
+// Bit i (i < 16) set iff byte i of the 16 is nonzero: the top bits, 128
+// each, are weighted by 1, 2, 4 .. 128 in a byte dot product over two words.
 __device__ __forceinline__ uint32_t nonzero_bytes16(uint4 b) {
-    return nonzero_bytes4(b.x) | (nonzero_bytes4(b.y) << 4) | (nonzero_bytes4(b.z) << 8) |
-           (nonzero_bytes4(b.w) << 12);
+    const uint32_t lo = __builtin_amdgcn_udot4(
+        nonzero_tops(b.y), 0x80402010u, __builtin_amdgcn_udot4(nonzero_tops(b.x), 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(
+        nonzero_tops(b.w), 0x80402010u, __builtin_amdgcn_udot4(nonzero_tops(b.z), 0x08040201u, 0u, false), false);
+    return (lo >> 7) | (hi << 1);
 }
 
 // Pixels [x, x + 16) of an image row of W bytes, zero past its end.  One
@@ -574,7 +573,7 @@ __device__ __forceinline__ uint64_t band_ends(uint64_t m, uint64_t s) { return m
 // line.  Nothing in it follows the lines one after the other: every touching
 // pair of intervals of neighbouring lines is known beforehand
 // (pair_requests), and each thread takes the pairs of eight columns of a
-// line.
+// line.  A root's entry is anything no smaller than its node.
 //   hooks      a pair is one LDS atomicMin that hooks the lower interval
 //              under the upper one; where it was hooked before, the two upper
 //              intervals are listed as a join
@@ -590,11 +589,12 @@ __device__ __forceinline__ uint64_t band_ends(uint64_t m, uint64_t s) { return m
 // in one long chain; local merge, both on one card: 4096 x 4096 p = 0.5,
 // 8-connectivity 28.0 us with the sweep, 22.4 so; 8192 x 8192 smoothed 63 and
 // 47; serpentine 56 and 32; 3001 x 4099 4-connectivity 18.6 and 15.6.
-template <int LINES, int NODES, int JOINS>
+template <int LINES, int NODES, int JOINS, int INFO>
 struct LineForest {
+    static constexpr bool kInfo = INFO > 0;
     uint32_t par[NODES];
     uint32_t join[JOINS];      // upper nodes of a join, 16 bits each
-    uint16_t info[NODES];      // line << 6 | first column of the interval
+    uint16_t info[INFO ? INFO : 1];  // line << 6 | first column of a node's interval (where kept)
     uint64_t E[LINES];         // interval ends
     uint64_t f[LINES], l[LINES], r[LINES];  // touching pairs with the line above
     uint16_t base[LINES];      // first node of the line
@@ -603,9 +603,10 @@ struct LineForest {
 };
 
 // First node at or after column 8 q of line k, and the nodes of its eight
-// columns' intervals, given the interval starts S.
-template <class F>
-__device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S) {
+// columns' intervals, given the interval starts S: every node a root, with
+// the entry root_entry(node, its first column).
+template <class F, class Entry>
+__device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S, Entry &&root_entry) {
     const uint64_t E = sh.E[k];
     const uint32_t e8 = (uint32_t)(E >> (8 * q)) & 0xFFu;
     const uint32_t first = (uint32_t)sh.base[k] + (uint32_t)__popcll(E & ((1ull << (8 * q)) - 1ull));
@@ -613,14 +614,14 @@ __device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S) {
     for (uint32_t s8 = (uint32_t)(S >> (8 * q)) & 0xFFu; s8; s8 &= s8 - 1u) {
         const uint32_t b = (uint32_t)__builtin_ctz(s8);
         const uint32_t n = first + (uint32_t)__builtin_popcount(e8 & ((1u << b) - 1u));
-        sh.info[n] = (uint16_t)(((uint32_t)k << 6) | ((uint32_t)q << 3) | b);
-        lds_st(&sh.par[n], n);
+        if (F::kInfo) sh.info[n] = (uint16_t)(((uint32_t)k << 6) | ((uint32_t)q << 3) | b);
+        lds_st(&sh.par[n], root_entry(n, 8u * (uint32_t)q + b));
     }
 }
 
 // Hooks of columns [8 q, 8 q + 8) of line k >= 1.
-template <bool DIAG, int LINES, int NODES, int JOINS>
-__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS> &sh, int k, int q) {
+template <bool DIAG, int LINES, int NODES, int JOINS, int INFO>
+__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS, INFO> &sh, int k, int q) {
     const int i = k * 8 + q;
     uint32_t m = ((const uint8_t *)sh.f)[i];
     if (DIAG) m |= ((uint32_t)((const uint8_t *)sh.l)[i] << 8) | ((uint32_t)((const uint8_t *)sh.r)[i] << 16);
@@ -635,7 +636,7 @@ __device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS> &sh
             else if (p >= 8u) up -= 1u;          // the one that ends left of b
         }
         const uint32_t old = atomicMin(&sh.par[lo], up);
-        if (old != lo && old != up) {
+        if (old < lo && old != up) {
             const uint32_t j = atomicAdd(&sh.joins, 1u);
             if (j < (uint32_t)JOINS) sh.join[j] = old | (up << 16);
             else lds_link(sh.par, old, up);
@@ -643,122 +644,30 @@ __device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS> &sh
     }
 }
 
-// Root of node n, whose owner alone stores to it, always an ancestor.  Stops
-// on any entry that is no smaller than its node.
-__device__ __forceinline__ uint32_t compress_node(uint32_t *par, uint32_t n) {
-    uint32_t p = lds_ld(&par[n]);
-    if (p >= n) return n;
-    while (true) {
-        const uint32_t g = lds_ld(&par[p]);
-        if (g >= p) return p;
-        p = g;
-        lds_st(&par[n], p);
-    }
+// Parent of node n, n itself for a root.
+__device__ __forceinline__ uint32_t parent_of(const uint32_t *par, uint32_t n) {
+    const uint32_t p = lds_ld(&par[n]);
+    return p < n ? p : n;
 }
 
-// ------------------------------------------- equal-value labeling (K1 part)
-//
-// Every in-image pixel takes part and a pixel joins the neighbours whose
-// image value equals its own (the kernels' literal test in Sec. II-A, all
-// value classes labeled).  Runs are maximal horizontal segments of one
-// value, so a row holds up to 64 of them.  `v` is a lane's pixel value, or
-// a value no byte can equal for lanes outside the image.
-
-// Sweep of one wavefront's band for equal-value labeling.  Each lane links
-// its run to the runs of the equal-valued cells above it (every such lane
-// proposes; the LDS atomicMin keeps the smallest root and the rare other
-// roots are joined by real unions).  Writes msk[r] = the row's run starts
-// and rinfo[r] (runs | 0x100: first run at column 0 | 0x200: last run ends
-// at column 63).
-template <int TH, int RPW, bool CONN8>
-__device__ __forceinline__ void sweep_band_eq(uint32_t *par, uint8_t *col, uint64_t *msk,
-                                              uint16_t *rinfo, const uint8_t *pix, int wave,
-                                              int lane, int wlim, int hlim) {
-    constexpr int SPR = slots_per_row<true>();
-    constexpr uint32_t kOut = 0x100u, kOutUp = 0x200u;
-    uint32_t ra = kNone, vu = kOutUp;
-    uint32_t pv[RPW];
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) pv[k] = pix[(wave * RPW + k) * kTileW + lane];
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-        const int r = wave * RPW + k;
-        const bool in = lane < wlim && r < hlim;
-        const uint32_t vv = in ? pv[k] : kOut;
-        const uint32_t vl = from_left(vv, kOut);
-        const uint64_t S = __ballot(in && (lane == 0 || vv != vl));
-        const bool isS = lane_in(S);
-        const uint32_t node = (uint32_t)(r * SPR) + bits_below(S) - (isS ? 0u : 1u);
-        uint32_t *pn = &par[node];
-        if (isS) {
-            lds_st(pn, node);
-            col[node] = (uint8_t)lane;
+// Points every node at its root and calls done(n) for the roots.  A node's
+// owner alone stores to it, always an ancestor, and a walk stops on any entry
+// that is no smaller than its node.  (Two walks at a time per thread, to
+// overlap their loads, measured slower: the kernel is short of issue slots.)
+template <int NT, class Done>
+__device__ __forceinline__ void compress_nodes(uint32_t *par, uint32_t nodes, Done &&done) {
+    for (uint32_t n = threadIdx.x; n < nodes; n += NT) {
+        uint32_t p = lds_ld(&par[n]);
+        if (p >= n) {
+            done(n);
+            continue;
         }
-        if (lane == 0) {
-            msk[r] = S;
-            rinfo[r] = (uint16_t)(__popcll(S) | ((S & 1ull) ? 0x100 : 0) | (wlim == 64 ? 0x200 : 0));
+        while (true) {
+            const uint32_t g = lds_ld(&par[p]);
+            if (g >= p) break;
+            p = g;
+            lds_st(&par[n], p);
         }
-        uint32_t md = in ? node : kNone;
-        if (k > 0) {
-            const uint32_t tM = in && vv == vu ? ra : kNone;
-            uint32_t tL = kNone, tR = kNone;
-            if (CONN8) {
-                const uint32_t vuL = from_left(vu, kOutUp), vuR = from_right(vu, kOutUp);
-                const uint32_t rL = from_left(ra, kNone), rR = from_right(ra, kNone);
-                tL = in && vv == vuL ? rL : kNone;
-                tR = in && vv == vuR ? rR : kNone;
-            }
-            const uint32_t tm = tM < tL ? (tM < tR ? tM : tR) : (tL < tR ? tL : tR);
-            if (tm != kNone) atomicMin(pn, tm);
-            if (in) md = lds_ld(pn);
-            const bool nM = tM != kNone && tM != md;
-            const bool nL = tL != kNone && tL != md;
-            const bool nR = tR != kNone && tR != md;
-            if (__ballot(nM || nL || nR)) {
-                // as in the binary sweep: one atomicMin per link, a general
-                // join only where the root was already linked elsewhere (a
-                // lane that finds md there met a duplicate of its own link)
-                uint32_t oM = 0, oL = 0, oR = 0;
-                if (nM) oM = atomicMin(&par[tM], md);
-                if (nL) oL = atomicMin(&par[tL], md);
-                if (nR) oR = atomicMin(&par[tR], md);
-                const bool rM = nM && oM < tM && oM != md;
-                const bool rL = nL && oL < tL && oL != md;
-                const bool rR = nR && oR < tR && oR != md;
-                if (__ballot(rM || rL || rR)) {
-                    if (rM) lds_link(par, md, oM);
-                    if (rL) lds_link(par, md, oL);
-                    if (rR) lds_link(par, md, oR);
-                }
-                if (in) md = lds_root(par, md);
-                if (isS) lds_st(pn, md);
-            }
-        }
-        ra = md;
-        vu = in ? vv : kOutUp;
-    }
-}
-
-// Band seam for equal-value labeling: the first row r of a band against the
-// last row of the band above (run starts already in msk), any forest state.
-template <bool CONN8>
-__device__ __forceinline__ void merge_seam_eq(uint32_t *par, const uint64_t *msk, const uint8_t *pix,
-                                              int r, int lane, int wlim, int hlim) {
-    constexpr int SPR = slots_per_row<true>();
-    constexpr uint32_t kOut = 0x100u, kOutUp = 0x200u;
-    if (r >= hlim) return;  // wave-uniform: the whole band lies below the image
-    const bool in = lane < wlim;
-    const uint32_t vv = in ? pix[r * kTileW + lane] : kOut;
-    const uint32_t vu = in ? pix[(r - 1) * kTileW + lane] : kOutUp;
-    const uint64_t S = uniform64(msk[r]), Su = uniform64(msk[r - 1]);
-    const uint32_t node = (uint32_t)(r * SPR) + bits_below(S) - (lane_in(S) ? 0u : 1u);
-    const uint32_t up = (uint32_t)((r - 1) * SPR) + bits_below(Su) - (lane_in(Su) ? 0u : 1u);
-    if (in && vv == vu) lds_link(par, node, up);
-    if (CONN8) {
-        const uint32_t vuL = from_left(vu, kOutUp), vuR = from_right(vu, kOutUp);
-        const uint32_t upL = from_left(up, kNone), upR = from_right(up, kNone);
-        if (in && vv == vuL) lds_link(par, node, upL);
-        if (in && vv == vuR) lds_link(par, node, upR);
     }
 }
 

@@ -33,34 +33,31 @@ namespace ccl {
 
 // Equal-value local merge (every value class labeled, Sec. II-A's
 // "same property" test): nodes are the runs of equal values of every row,
-// 64 slots per row, swept row by row (sweep_band_eq).
+// lines are rows, and touching pairs are those of equal value.  2160 x 3840
+// in six levels, 8-connectivity: 24 us; sweeping the rows of each wavefront
+// one after the other took 39.5.
 template <int TH>
 struct K1EqLds {
-    static constexpr int SPR = slots_per_row<true>();
-    uint32_t par[TH * SPR];                // run-indexed parents
-    uint8_t col[TH * SPR];                 // every run's first column (node n lies in row n / 64)
-    uint64_t msk[TH];                      // per row: run starts
-    uint64_t flg[TH];                      // per row: local roots of edge-touching components
-    uint16_t rinfo[TH];                    // runs | 0x100: first run at column 0 | 0x200: last ends at 63
+    LineForest<TH, TH * 64, 16 * TH, 0> f;
+    uint64_t S[TH];         // per row: run starts
+    uint64_t flg[TH];       // per row: local roots of edge-touching components
     alignas(16) uint8_t pix[TH * kTileW];  // the tile's bytes
+    uint32_t nodes;
 };
 
 // Kernel 1 body for tile t of image v, equal-value labeling.  Ends after a
 // workgroup barrier, so the caller may reuse the LDS for another tile.
 template <int TH, int NW, bool CONN8>
 __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds<TH> &sh) {
+    static_assert(TH <= 64, "one lane per row");
     constexpr int SPR = slots_per_row<true>();
     constexpr int RPW = TH / NW;
     constexpr int NT = NW * 64;
     constexpr int CH = TH * 4;                  // 16-byte chunks per tile
     constexpr int LPT = (CH + NT - 1) / NT;     // chunks per thread
-    constexpr int NODES = TH * SPR;             // run-indexed nodes per tile
-    constexpr int NPT = (NODES + NT - 1) / NT;  // nodes per thread
-    uint32_t *par = sh.par;
-    uint8_t *col = sh.col;
-    uint64_t *msk = sh.msk;
+    auto &F = sh.f;
+    uint32_t *par = F.par;
     uint64_t *flg = sh.flg;
-    uint16_t *rinfo = sh.rinfo;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
     const uint32_t TX = (uint32_t)v.tilesX;
@@ -69,6 +66,7 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
     const bool hasLeft = tx > 0, hasRight = tx + 1 < v.tilesX;
     // columns / rows of the tile inside the image
     const int wlim = min(kTileW, v.W - tx * kTileW), hlim = min(TH, v.H - ty * TH);
+    const uint64_t cols = wlim == 64 ? ~0ull : ((1ull << wlim) - 1ull);
 
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
@@ -76,79 +74,149 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
         if (c < CH) ((uint4 *)sh.pix)[c] = load_chunk(v, tx, ty, TH, c >> 2, c & 3);
     }
     if (tid < TH) flg[tid] = 0ull;
+    if (tid == 0) F.joins = 0u;
     __syncthreads();
-    sweep_band_eq<TH, RPW, CONN8>(par, col, msk, rinfo, sh.pix, wave, lane, wlim, hlim);
-    if (NW > 1) {
-        __syncthreads();
-        if (wave > 0) merge_seam_eq<CONN8>(par, msk, sh.pix, wave * RPW, lane, wlim, hlim);
-    }
-    __syncthreads();
-
-    // node-parallel finish: every node finds its root (read-only walk) and
-    // its owner alone stores it, so par[n] is the root afterwards; the run's
-    // record (the root's tile-local pixel) goes out
-    uint16_t *sl = v.slots + (size_t)t * TH * SPR;
+    // run starts of every row, and which columns equal the row above
+    // straight, to its left and to its right (held in the forest's pair
+    // masks until the pairs are known); 16 columns per thread, compared by
+    // bytes
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) {
-        const int n = tid + i * NT;
-        // the numbering leaves unused slots at the end of each row
-        if (n % SPR >= (int)(rinfo[n / SPR] & 0x7Fu)) continue;
-        const uint32_t root = lds_root(par, (uint32_t)n);
-        if (root != (uint32_t)n) lds_st(&par[n], root);
-        sl[n] = (uint16_t)((root / SPR) * kTileW + col[root]);
+    for (int i = 0; i < LPT; ++i) {
+        const int c = tid + i * NT;
+        if (c >= CH) break;
+        const int r = c >> 2, q = c & 3;
+        const uint8_t *pr = sh.pix + r * kTileW + q * 16, *pu = pr - (r > 0 ? kTileW : 0);
+        const uint4 w = *(const uint4 *)pr, u = *(const uint4 *)pu;
+        // the 16 bytes one column to the left / right (what lies beyond the
+        // tile's columns is masked)
+        auto left = [](uint4 x, uint32_t before) {
+            return make_uint4((x.x << 8) | before, __builtin_amdgcn_alignbyte(x.y, x.x, 3),
+                              __builtin_amdgcn_alignbyte(x.z, x.y, 3), __builtin_amdgcn_alignbyte(x.w, x.z, 3));
+        };
+        auto right = [](uint4 x, uint32_t after) {
+            return make_uint4(__builtin_amdgcn_alignbyte(x.y, x.x, 1), __builtin_amdgcn_alignbyte(x.z, x.y, 1),
+                              __builtin_amdgcn_alignbyte(x.w, x.z, 1), (x.w >> 8) | (after << 24));
+        };
+        auto differ = [](uint4 x, uint4 y) {
+            return nonzero_bytes16(make_uint4(x.x ^ y.x, x.y ^ y.y, x.z ^ y.z, x.w ^ y.w));
+        };
+        const uint32_t in = r < hlim ? (uint32_t)(cols >> (16 * q)) & 0xFFFFu : 0u;
+        const uint32_t inu = r > 0 ? in : 0u;
+        const uint32_t first = q == 0 ? 1u : 0u;  // column 0 is in this chunk
+        ((uint16_t *)sh.S)[c] = (uint16_t)((differ(w, left(w, q > 0 ? pr[-1] : 0u)) | first) & in);
+        ((uint16_t *)F.f)[c] = (uint16_t)(~differ(w, u) & inu);
+        if (CONN8) {
+            const uint32_t last = (uint32_t)((cols >> 1) >> (16 * q)) & 0xFFFFu;  // columns with a right neighbour
+            ((uint16_t *)F.l)[c] = (uint16_t)(~differ(w, left(u, q > 0 ? pu[-1] : 0u)) & inu & ~first);
+            ((uint16_t *)F.r)[c] = (uint16_t)(~differ(w, right(u, q < 3 ? pu[16] : 0u)) & inu & last);
+        } else {
+            ((uint16_t *)F.l)[c] = 0;
+            ((uint16_t *)F.r)[c] = 0;
+        }
     }
     __syncthreads();
-    if (tid < TH) v.rowmask[(size_t)t * rowmask_words(TH) + tid] = msk[tid];
+    // runs numbered densely, row by row; the touching pairs of every row
+    // with the row above (lane = row)
+    if (wave == 0) {
+        const uint64_t S = lane < TH ? sh.S[lane] : 0ull, Su = lane > 0 && lane < TH ? sh.S[lane - 1] : 0ull;
+        const uint64_t M = lane < hlim ? cols : 0ull;
+        const uint64_t E = band_ends(M, S), Eu = band_ends(cols, Su);
+        uint32_t nodes;
+        const uint32_t b = wave_exclusive_scan((uint32_t)__popcll(S), &nodes);
+        if (lane < TH) {
+            F.E[lane] = E;
+            F.base[lane] = (uint16_t)b;
+            const PairRequests q = pair_requests(F.f[lane], F.l[lane], F.r[lane], M, S, E, cols, Su, Eu);
+            F.f[lane] = q.f;
+            F.l[lane] = q.l;
+            F.r[lane] = q.r;
+        }
+        if (lane == 0) sh.nodes = nodes;
+    }
+    __syncthreads();
+    // a root's entry is kPixel | its first pixel, the smallest of its
+    // component (runs are numbered in raster order)
+    constexpr uint32_t kPixel = 0x80000000u;
+    for (int i = tid; i < TH * 8; i += NT)
+        forest_nodes(F, i >> 3, i & 7, sh.S[i >> 3],
+                     [&](uint32_t, uint32_t c) { return kPixel | (uint32_t)((i >> 3) * kTileW) | c; });
+    __syncthreads();
+    for (int i = tid; i < TH * 8; i += NT)
+        if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
+    __syncthreads();
+    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
+    if (joins) {  // workgroup-uniform
+        compress_nodes<NT>(par, nodes, [](uint32_t) {});
+        __syncthreads();
+        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
+            const uint32_t e = F.join[i];
+            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
+        }
+        __syncthreads();
+    }
+    compress_nodes<NT>(par, nodes, [](uint32_t) {});
+    __syncthreads();
+    // records: the first pixel of the node's component
+    uint16_t *sl = v.slots + (size_t)t * TH * SPR;
+    for (int i = tid; i < TH * 8; i += NT) {
+        const int r = i >> 3, q = i & 7;
+        const uint32_t first = F.pre[i], base = F.base[r], e8 = ((const uint8_t *)F.E)[i];
+        for (uint32_t s8 = (uint32_t)(sh.S[r] >> (8 * q)) & 0xFFu; s8; s8 &= s8 - 1u) {
+            const uint32_t n = first + (uint32_t)__builtin_popcount(e8 & ((1u << __builtin_ctz(s8)) - 1u));
+            uint32_t e = lds_ld(&par[n]);
+            if (e < kPixel) {
+                e = lds_ld(&par[e]);
+                lds_st(&par[n], e);  // read below by edge cells; its own thread alone reads it before
+            }
+            sl[r * SPR + (int)(n - base)] = (uint16_t)e;
+        }
+    }
+    __syncthreads();
+    uint64_t *rw = v.rowmask + (size_t)t * rowmask_words(TH);
+    if (tid < TH) rw[tid] = sh.S[tid];
     // edge masks and edge-cell roots for the boundary analysis; every such
     // root is seeded in the forest (lanes of one component store the same
-    // word)
-    if (wave == 0) {
+    // word) and marked in the edge-root masks.  Edge k goes to wavefront
+    // k mod NW.
+    {
         uint64_t *mk = v.masks + (size_t)t * mask_words(TH);
         uint32_t *rt = v.roots + (size_t)t * roots_per_tile(TH);
-        // cells taking part in the top / bottom row, run starts of those rows
-        const uint64_t cols = wlim == 64 ? ~0ull : ((1ull << wlim) - 1ull);
+        // cells taking part in the top / bottom row
         const uint64_t mTop = cols, mBot = TH - 1 < hlim ? cols : 0ull;
-        const uint64_t sTop = uniform64(msk[0]), sBot = uniform64(msk[TH - 1]);
-        // global index of the root pixel of run node n; the root is marked
-        // in the edge-root masks (its component touches a shared edge)
         auto root_g = [&](uint32_t n) {
-            const uint32_t root = lds_ld(&par[n]);
-            const uint32_t rr = root / SPR, rc = col[root];
-            atomicOr((unsigned long long *)&flg[rr], 1ull << rc);
-            return global_index(v, tx, ty, TH, rr * kTileW + rc);
+            const uint32_t pos = lds_ld(&par[n]) & (kPixel - 1u);
+            atomicOr((unsigned long long *)&flg[pos >> 6], 1ull << (pos & 63u));
+            return global_index(v, tx, ty, TH, pos);
         };
         auto put = [&](uint32_t *dst, uint32_t g) {
             *dst = g;
             v.labels[g] = g + 1u;
         };
-        if (hasUp && lane_in(mTop)) {
-            const uint32_t n = bits_below(sTop) - (lane_in(sTop) ? 0u : 1u);
-            put(&rt[roots_top(TH) + lane], root_g(n));
+        if (wave == 0) {
+            if (hasUp && lane_in(mTop)) put(&rt[roots_top(TH) + lane], root_g(bits_below(uniform64(F.E[0]))));
+            if (lane == 0) {
+                mk[kMaskTop] = mTop;
+                mk[kMaskBottom] = mBot;
+            }
         }
-        if (hasDown && lane_in(mBot)) {
-            const uint32_t n = (uint32_t)((TH - 1) * SPR) + bits_below(sBot) - (lane_in(sBot) ? 0u : 1u);
-            put(&rt[roots_bottom(TH) + lane], root_g(n));
+        if (wave == 1 % NW && hasDown && lane_in(mBot))
+            put(&rt[roots_bottom(TH) + lane], root_g((uint32_t)F.base[TH - 1] + bits_below(uniform64(F.E[TH - 1]))));
+        // per row (lane = row): cells in the left / right column
+        const bool lb = lane < hlim, rb = lb && wlim == 64;
+        if (wave == 2 % NW) {
+            if (hasLeft && lb) put(&rt[roots_left(TH) + lane], root_g((uint32_t)F.base[lane]));
+            const uint64_t m = __ballot(lb);
+            if (lane == 0) mk[kMaskLeft] = m;
         }
-        // per row (lane = row): cells in the left / right column, last run
-        const uint64_t mr = lane < TH ? msk[lane] : 0ull;
-        const bool rowIn = lane < hlim;
-        const bool lb = rowIn, rb = rowIn && wlim == 64;
-        const uint32_t first = (uint32_t)(lane * SPR), lastRun = (uint32_t)__popcll(mr) - 1u;
-        const uint64_t mLeft = __ballot(lb), mRight = __ballot(rb);
-        if (hasLeft && lb) put(&rt[roots_left(TH) + lane], root_g(first));
-        if (hasRight && rb) put(&rt[roots_right(TH) + lane], root_g(first + lastRun));
-        if (lane == 0) {
-            mk[kMaskTop] = mTop;
-            mk[kMaskBottom] = mBot;
-            mk[kMaskLeft] = mLeft;
-            mk[mask_right(TH)] = mRight;
+        if (wave == 3 % NW) {
+            if (hasRight && rb)
+                put(&rt[roots_right(TH) + lane], root_g((uint32_t)F.base[lane] + (uint32_t)__popcll(sh.S[lane]) - 1u));
+            const uint64_t m = __ballot(rb);
+            if (lane == 0) mk[mask_right(TH)] = m;
         }
-        // only this wavefront marks edge roots: once its own LDS operations
-        // have completed, the masks are whole
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        if (lane < TH) v.rowmask[(size_t)t * rowmask_words(TH) + TH + lane] = flg[lane];
     }
+    __syncthreads();  // every wavefront's marks are in
+    if (tid < TH) rw[TH + tid] = flg[tid];
     __syncthreads();  // LDS may be reused for another tile
 }
 
@@ -157,7 +225,7 @@ template <int TH, bool CONN8>
 struct K1BandLds {
     static constexpr int NB = TH / 2;
     static constexpr int NODES = NB * (CONN8 ? 32 : 64);  // a band's most intervals
-    LineForest<NB, NODES, 16 * TH> f;
+    LineForest<NB, NODES, 16 * TH, NODES> f;
     uint64_t msk[TH];  // per row: foreground mask
     uint64_t flg[TH];  // per row: local roots of edge-touching components
     uint32_t nodes;
@@ -224,7 +292,8 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
     }
     for (int i = tid; i < NB * 8; i += NT) {
         const int k = i >> 3;
-        forest_nodes(F, k, i & 7, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]));
+        forest_nodes(F, k, i & 7, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]),
+                     [](uint32_t n, uint32_t) { return n; });
     }
     __syncthreads();
     for (int i = tid; i < NB * 8; i += NT)
@@ -232,11 +301,11 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
     __syncthreads();
     const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
     if (joins) {  // workgroup-uniform
-        for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) compress_node(par, n);
+        compress_nodes<NT>(par, nodes, [](uint32_t) {});
         __syncthreads();
         for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
             const uint32_t e = F.join[i];
-            lds_link(par, lds_ld(&par[e & 0xFFFFu]), lds_ld(&par[e >> 16]));
+            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
         }
         __syncthreads();
     }
@@ -253,8 +322,7 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
     // pixel, which walks still take for a root's (it is no smaller than any
     // node)
     constexpr uint32_t kPixel = 0x80000000u;
-    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT)
-        if (compress_node(par, n) == n) lds_st(&par[n], kPixel | smallest(n));
+    compress_nodes<NT>(par, nodes, [&](uint32_t n) { lds_st(&par[n], kPixel | smallest(n)); });
     __syncthreads();
     // a root without a top-row pixel: the component's smallest pixel may be
     // the top-row pixel of another of its intervals in the band (once one
