@@ -7,15 +7,18 @@
 // Roots are numbered in raster order, so records come out in increasing
 // label order:
 //   st_roots     one 64-bit root mask per 64-pixel row word (lane = pixel)
-//                and the number of roots per block of 64 words;
-//   st_scan      exclusive scan of the block counts (one workgroup), total;
+//                and the number of roots per block of 256 words;
+//   st_scan      exclusive scan of the block counts (one workgroup); only for
+//                images of many blocks, in others every block of st_bases
+//                adds up the counts before its own;
 //   st_bases     exclusive scan inside each block: the first record index
 //                of every word, and the records of its roots initialised;
-//   st_accum     every run of equal labels in a row adds its length,
-//                extent and coordinate sums to its component's record: first
-//                into a hash table in LDS keyed by label per 64 x 256 block
-//                (a large component has thousands of runs, which would
-//                otherwise all hit one record), then once per table slot
+//                the total;
+//   st_accum     a wavefront takes 16 rows of a 64-pixel column and gathers
+//                the labels that fill much of it one at a time, from lane
+//                masks; what is left goes run by run (runs of equal labels in
+//                a row).  Both add to a hash table in LDS keyed by label per
+//                128 x 256 block, which is added to the records once per slot
 //                with global atomics.
 #include <hip/hip_runtime.h>
 
@@ -27,33 +30,54 @@ namespace ccl {
 
 namespace {
 
-constexpr int kWordsPerBlock = 64;
+constexpr int kWordsPerBlock = 256;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 
 __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, uint32_t WW,
                                                  uint32_t words, uint64_t *mask, uint32_t *bsum) {
     __shared__ uint32_t part[4];
-    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    constexpr int kWords = kWordsPerBlock / 4, kBatch = 16;
     uint32_t cnt = 0;
-    for (int i = 0; i < kWordsPerBlock / 4; ++i) {
-        const uint32_t w = blockIdx.x * kWordsPerBlock + (uint32_t)(wave * (kWordsPerBlock / 4) + i);
-        if (w >= words) break;  // wave-uniform
-        const uint32_t y = w / WW, x = (w % WW) * (uint32_t)kTileW + (uint32_t)lane;
-        bool root = false;
-        if (x < W) {
-            const uint32_t p = y * W + x;
-            root = L[p] == p + 1u;
+#pragma unroll 1
+    for (int i0 = 0; i0 < kWords; i0 += kBatch) {
+        const uint32_t w0 = blockIdx.x * kWordsPerBlock + (uint32_t)(wave * kWords + i0);
+        if (w0 >= words) break;  // wave-uniform
+        uint32_t y = w0 / WW, wx = w0 - y * WW;
+        // the batch's loads are in flight together
+        uint32_t l[kBatch], p[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const uint32_t x = wx * (uint32_t)kTileW + (uint32_t)lane;
+            const bool in = w0 + (uint32_t)i < words && x < W;
+            p[i] = y * W + x;
+            l[i] = in ? L[p[i]] : 0u;
+            if (++wx == WW) {
+                wx = 0u;
+                ++y;
+            }
         }
-        const uint64_t m = __ballot(root);
-        if (lane == 0) mask[w] = m;
-        cnt += (uint32_t)__popcll(m);
+        uint64_t mine = 0ull;  // lane i: word i's mask
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const uint64_t m = __ballot(l[i] == p[i] + 1u);
+            if (lane == i) mine = m;
+            cnt += (uint32_t)__popcll(m);
+        }
+        if (lane < kBatch && w0 + (uint32_t)lane < words) mask[w0 + (uint32_t)lane] = mine;
     }
     if (lane == 0) part[wave] = cnt;
     __syncthreads();
     if (threadIdx.x == 0) bsum[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-__global__ void __launch_bounds__(1024) st_scan(uint32_t *bsum, uint32_t nb, uint32_t *n_out) {
+// Blocks whose counts every block of st_bases adds up by itself.  The sums
+// read nb * nb / 2 counts from the L2, 8 MB at 2048 blocks (128 Mpixels);
+// a scan in a launch of its own takes 4 to 5 us whatever the size.
+constexpr uint32_t kSelfScanBlocks = 2048u;
+
+__global__ void __launch_bounds__(1024) st_scan(uint32_t *bsum, uint32_t nb) {
     __shared__ uint32_t s[1024];
     const uint32_t tid = threadIdx.x;
     const uint32_t per = (nb + 1023u) / 1024u;
@@ -74,25 +98,43 @@ __global__ void __launch_bounds__(1024) st_scan(uint32_t *bsum, uint32_t nb, uin
         bsum[b] = run;
         run += t;
     }
-    if (tid == 1023u) *n_out = s[1023];
 }
 
-__global__ void __launch_bounds__(64) st_bases(const uint64_t *mask, const uint32_t *bsum,
+// SELF: bsum holds the blocks' counts, else their exclusive prefix.
+template <bool SELF>
+__global__ void __launch_bounds__(kWordsPerBlock) st_bases(const uint64_t *mask, const uint32_t *bsum,
                                                 uint32_t words, uint32_t W, uint32_t WW,
-                                                uint32_t *base, ccl_component *out, uint32_t cap) {
-    const int lane = (int)(threadIdx.x & 63);
-    const uint32_t w = blockIdx.x * kWordsPerBlock + (uint32_t)lane;
+                                                uint32_t *base, ccl_component *out, uint32_t cap,
+                                                uint32_t *n_out) {
+    __shared__ uint32_t part[2][4];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t w = blockIdx.x * kWordsPerBlock + tid;
     const uint64_t m = w < words ? mask[w] : 0ull;
-    const uint32_t c = (uint32_t)__popcll(m);
-    uint32_t x = c;  // inclusive scan over the 64 words of the block
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_up((int)x, off, 64);
-        if (lane >= off) x += t;
+    uint32_t before = 0u;
+    if (SELF) {
+        for (uint32_t j = tid; j < blockIdx.x; j += kWordsPerBlock) before += bsum[j];
+        wave_exclusive_scan(before, &before);
     }
+    uint32_t wtot;
+    const uint32_t ex = wave_exclusive_scan((uint32_t)__popcll(m), &wtot);
+    if (lane == 0) {
+        part[0][wave] = before;
+        part[1][wave] = wtot;
+    }
+    __syncthreads();
+    uint32_t b = SELF ? 0u : bsum[blockIdx.x], total = 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) {
+        if (SELF) b += part[0][j];
+        total += part[1][j];
+    }
+    if (blockIdx.x + 1u == gridDim.x && tid == 0) *n_out = b + total;
+    b += ex;
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) b += j < wave ? part[1][j] : 0u;
     if (w >= words) return;
-    const uint32_t b = bsum[blockIdx.x] + x - c;
     base[w] = b;
-    const uint32_t p0 = (w / WW) * W + (w % WW) * (uint32_t)kTileW;
+    const uint32_t y = w / WW, p0 = y * W + (w - y * WW) * (uint32_t)kTileW;
     uint64_t mm = m;
     uint32_t id = b;
     while (mm) {
@@ -124,28 +166,6 @@ __device__ __forceinline__ void add_global(ccl_component &r, uint32_t len, uint3
     atomicAdd((unsigned long long *)&r.sum_y, (unsigned long long)syv);
 }
 
-// Reductions over the 64 lanes of a wavefront.
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o, 64);
-    return v;
-}
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, o, 64);
-        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), o, 64);
-        v += ((uint64_t)hi << 32) | lo;
-    }
-    return v;
-}
-
 // Record index of the component whose root pixel is r (its label - 1).
 __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t WW,
                                               const uint64_t *mask, const uint32_t *base) {
@@ -154,37 +174,63 @@ __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t W
     return base[w] + (uint32_t)__popcll(mask[w] & ((1ull << (rx & 63u)) - 1ull));
 }
 
-// Block of 64 columns x kAccRows rows, 16 wavefronts of 16 rows each.  The
-// hash table is keyed by label, so a run needs no global read; the record
-// index is looked up once per table slot when the block flushes.
-constexpr int kAccWaves = 16, kAccRowsPerWave = 16, kAccRows = kAccWaves * kAccRowsPerWave;
-constexpr int kAccSlots = 1024;
+// Block of 128 x 256 pixels, a wavefront per 64 columns and 32 rows.  The hash
+// table is keyed by label, so an addition needs no global read; the record
+// index is looked up once per table slot when the block flushes.  Bound by the
+// flushes of components that reach many blocks (atomics on one record follow
+// each other), hence few large blocks, about one per compute unit at 8
+// Mpixels, and a table for all the small components such a block may hold.
+// Gathering a label over a wavefront's strip makes its eight LDS additions
+// once per strip instead of once per row.  At most 80 scalar registers (eight
+// wavefronts per SIMD), so that two workgroups share a compute unit.
+// 2160 x 3840 smoothed labels: 27.6 us; adding run by run in blocks of 64 x 256
+// took 46.  Blocks of 128 x 128 took 33.4 (twice the flushes), eight
+// wavefronts per block 31.0.
+constexpr int kAccWaves = 16, kAccStripRows = 16, kAccStrips = 2;
+constexpr int kAccCols = 2 * kTileW, kAccRows = kAccWaves / 2 * kAccStripRows * kAccStrips;
+constexpr int kAccSlots = 2048;
+// Labels gathered over the strip at most (1, 2, 4 and 8 measured 28.1, 27.6,
+// 29.0 and 30.3 us), and the pixels a gathered label must have had for another
+// one to be tried: a strip of small components is cheaper run by run.
+constexpr int kAccGather = 2;
+constexpr uint32_t kAccGatherPixels = 24u;
 
-__global__ void __launch_bounds__(kAccWaves * 64) st_accum(const uint32_t *L, uint32_t H, uint32_t W,
+__global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L, uint32_t H, uint32_t W,
                                                           uint32_t WW, const uint64_t *mask,
                                                           const uint32_t *base, ccl_component *out,
                                                           uint32_t cap) {
+    // extents and sums relative to the block's first pixel (a sum is at most
+    // 2^15 * 255)
     __shared__ uint32_t key[kAccSlots], area[kAccSlots], xmn[kAccSlots], ymn[kAccSlots],
-        xmx[kAccSlots], ymx[kAccSlots];
-    __shared__ unsigned long long sx[kAccSlots], sy[kAccSlots];
+        xmx[kAccSlots], ymx[kAccSlots], sx[kAccSlots], sy[kAccSlots];
     constexpr int NT = kAccWaves * 64;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int i = tid; i < kAccSlots; i += NT) {
         key[i] = kEmpty;
         area[i] = 0u;
         xmn[i] = ymn[i] = 0xFFFFFFFFu;
         xmx[i] = ymx[i] = 0u;
-        sx[i] = sy[i] = 0ull;
+        sx[i] = sy[i] = 0u;
     }
     __syncthreads();
-    const uint32_t x0 = blockIdx.x * (uint32_t)kTileW, y0 = blockIdx.y * (uint32_t)kAccRows;
+    const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * (uint32_t)kAccRows;
+    const uint32_t xr = (uint32_t)(wave & 1) * kTileW;  // the wavefront's first column and row in the block
+    const uint32_t yr = (uint32_t)(wave >> 1) * (kAccStripRows * kAccStrips);
     const uint32_t n = H * W;
-    const uint32_t x = x0 + (uint32_t)lane;
+    const uint32_t x = bx + xr + (uint32_t)lane;
     const bool xin = x < W;
-    // Adds one run (or a wave's partial record) to the LDS table.
+    auto to_record = [&](uint32_t l, uint32_t len, uint32_t xa, uint32_t xb, uint32_t ya, uint32_t yb,
+                         uint32_t sxv, uint32_t syv) {
+        const uint32_t id = record_of(l - 1u, W, WW, mask, base);
+        if (id < cap)
+            add_global(out[id], len, bx + xa, bx + xb, by + ya, by + yb, (uint64_t)len * bx + sxv,
+                       (uint64_t)len * by + syv);
+    };
+    // Adds one run (or a strip's pixels of one label) to the LDS table.
     auto add_lds = [&](uint32_t l, uint32_t len, uint32_t xa, uint32_t xb, uint32_t ya, uint32_t yb,
-                       uint64_t sxv, uint64_t syv) {
-        uint32_t h = (l * 2654435761u) >> 22;  // 10 bits
+                       uint32_t sxv, uint32_t syv) {
+        uint32_t h = (l * 2654435761u) >> 21;  // 11 bits
         for (int probe = 0; probe < 16; ++probe) {
             const uint32_t kk = atomicCAS(&key[h], kEmpty, l);
             if (kk == kEmpty || kk == l) {
@@ -193,76 +239,77 @@ __global__ void __launch_bounds__(kAccWaves * 64) st_accum(const uint32_t *L, ui
                 atomicMax(&xmx[h], xb);
                 atomicMin(&ymn[h], ya);
                 atomicMax(&ymx[h], yb);
-                atomicAdd(&sx[h], (unsigned long long)sxv);
-                atomicAdd(&sy[h], (unsigned long long)syv);
+                atomicAdd(&sx[h], sxv);
+                atomicAdd(&sy[h], syv);
                 return;
             }
             h = (h + 1u) & (uint32_t)(kAccSlots - 1);
         }
         // table full around h: straight to the record
-        const uint32_t id = record_of(l - 1u, W, WW, mask, base);
-        if (id < cap) add_global(out[id], len, xa, xb, ya, yb, sxv, syv);
+        to_record(l, len, xa, xb, ya, yb, sxv, syv);
     };
-    // A large component has runs in most rows, which would all meet on one
-    // table slot: the runs of the wavefront's "hot" label (the smallest
-    // label starting a run in its first row with one, which is a large
-    // component's in noise) add into per-lane registers instead, reduced
-    // over the wavefront once at the end.
-    uint32_t hot = kEmpty;
-    uint32_t hA = 0u, hXa = 0xFFFFFFFFu, hXb = 0u, hYa = 0xFFFFFFFFu, hYb = 0u;
-    uint64_t hSx = 0ull, hSy = 0ull;
-    // all the wavefront's rows are loaded first, so the loads overlap
-    uint32_t lv[kAccRowsPerWave];
+#pragma unroll 1
+    for (uint32_t yw = yr; yw < yr + kAccStripRows * kAccStrips && by + yw < H; yw += kAccStripRows) {
+        // all the strip's rows are loaded first, so the loads overlap
+        uint32_t lv[kAccStripRows];
 #pragma unroll
-    for (int k = 0; k < kAccRowsPerWave; ++k) {
-        const uint32_t y = y0 + (uint32_t)(wave * kAccRowsPerWave + k);
-        lv[k] = xin && y < H ? L[y * W + x] : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kAccRowsPerWave; ++k) {
-        const uint32_t y = y0 + (uint32_t)(wave * kAccRowsPerWave + k);
-        if (y >= H) break;  // wave-uniform
-        const uint32_t l = lv[k];
-        const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
-        const bool start = l != 0u && l != ll && l <= n;  // (labels above H*W: not canonical)
-        const uint64_t S = __ballot(start);
-        const uint64_t E = __ballot(l != 0u && l != lr);
-        if (hot == kEmpty && S) hot = wave_min_u32(start ? l : kEmpty);  // wave-uniform
-        if (!start) continue;
-        // this lane starts a run of equal labels; it ends at the first run
-        // end at or after it
-        const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
-        const uint32_t len = e - (uint32_t)lane + 1u, x1 = x0 + e;
-        const uint64_t sxv = (uint64_t)len * ((uint64_t)x + (uint64_t)x1) / 2u;
-        const uint64_t syv = (uint64_t)len * (uint64_t)y;
-        if (l == hot) {
-            hA += len;
-            hXa = min(hXa, x);
-            hXb = max(hXb, x1);
-            hYa = min(hYa, y);
-            hYb = max(hYb, y);
-            hSx += sxv;
-            hSy += syv;
-        } else {
-            add_lds(l, len, x, x1, y, y, sxv, syv);
+        for (int k = 0; k < kAccStripRows; ++k) {
+            const uint32_t y = by + yw + (uint32_t)k;
+            const uint32_t l = xin && y < H ? L[y * W + x] : 0u;
+            lv[k] = l <= n ? l : 0u;  // (labels above H*W: not canonical)
         }
-    }
-    if (hot != kEmpty) {  // wave-uniform
-        hA = wave_sum_u32(hA);
-        hXa = wave_min_u32(hXa);
-        hXb = wave_max_u32(hXb);
-        hYa = wave_min_u32(hYa);
-        hYb = wave_max_u32(hYb);
-        hSx = wave_sum_u64(hSx);
-        hSy = wave_sum_u64(hSy);
-        if (lane == 0 && hA != 0u) add_lds(hot, hA, hXa, hXb, hYa, hYb, hSx, hSy);
+#pragma unroll 1
+        for (int g = 0; g < kAccGather; ++g) {
+            // a label still in the strip: the topmost one of the first column
+            // that has any
+            uint32_t c = 0u;
+#pragma unroll
+            for (int k = kAccStripRows - 1; k >= 0; --k) c = lv[k] ? lv[k] : c;
+            const uint64_t any = __ballot(c != 0u);
+            if (!any) break;
+            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)c, __builtin_ctzll(any));
+            // its pixels per column (lanes) and per row; they leave the strip
+            uint32_t cnt = 0u, area = 0u, sr = 0u, ymask = 0u;
+            uint64_t xmask = 0ull;
+#pragma unroll
+            for (int k = kAccStripRows - 1; k >= 0; --k) {
+                const bool is = lv[k] == l;
+                const uint64_t m = __ballot(is);
+                cnt += is ? 1u : 0u;
+                lv[k] = is ? 0u : lv[k];
+                xmask |= m;
+                ymask |= m ? 1u << k : 0u;
+                area += (uint32_t)__popcll(m);
+                if (k > 0) sr += area;  // the pixels of rows >= k, summed over k >= 1: every pixel's row
+            }
+            uint32_t sc;  // column sum, at most 16 * 2016
+            wave_exclusive_scan(cnt * (uint32_t)lane, &sc);
+            if (lane == 0)
+                add_lds(l, area, xr + (uint32_t)__builtin_ctzll(xmask), xr + 63u - (uint32_t)__builtin_clzll(xmask),
+                        yw + (uint32_t)__builtin_ctz(ymask), yw + 31u - (uint32_t)__builtin_clz(ymask),
+                        area * xr + sc, area * yw + sr);
+            if (area < kAccGatherPixels) break;
+        }
+#pragma unroll
+        for (int k = 0; k < kAccStripRows; ++k) {
+            const uint32_t y = yw + (uint32_t)k;
+            const uint32_t l = lv[k];
+            const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
+            const uint64_t E = __ballot(l != 0u && l != lr);
+            if (!E) continue;  // wave-uniform
+            if (l == 0u || l == ll) continue;
+            // this lane starts a run of equal labels; it ends at the first run
+            // end at or after it
+            const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
+            const uint32_t len = e - (uint32_t)lane + 1u, xa = xr + (uint32_t)lane, xb = xr + e;
+            add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
+        }
     }
     __syncthreads();
     for (int i = tid; i < kAccSlots; i += NT) {
         const uint32_t l = key[i];
         if (l == kEmpty) continue;
-        const uint32_t id = record_of(l - 1u, W, WW, mask, base);
-        if (id < cap) add_global(out[id], area[i], xmn[i], xmx[i], ymn[i], ymx[i], sx[i], sy[i]);
+        to_record(l, area[i], xmn[i], xmx[i], ymn[i], ymx[i], sx[i], sy[i]);
     }
 }
 
@@ -300,10 +347,15 @@ extern "C" int ccl_component_stats(const uint32_t *labels, int32_t H, int32_t W,
     uint32_t *bsum = (uint32_t *)((char *)base + align_up((size_t)words * sizeof(uint32_t), 256));
     const uint32_t cap = capacity > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)capacity;
     hipLaunchKernelGGL(st_roots, dim3(nb), dim3(256), 0, s, labels, (uint32_t)W, WW, words, mask, bsum);
-    hipLaunchKernelGGL(st_scan, dim3(1), dim3(1024), 0, s, bsum, nb, n_out);
-    hipLaunchKernelGGL(st_bases, dim3(nb), dim3(64), 0, s, mask, bsum, words, (uint32_t)W, WW, base,
-                       out, cap);
-    hipLaunchKernelGGL(st_accum, dim3(WW, ((uint32_t)H + kAccRows - 1u) / kAccRows), dim3(kAccWaves * 64),
+    if (nb <= kSelfScanBlocks) {
+        hipLaunchKernelGGL(st_bases<true>, dim3(nb), dim3(kWordsPerBlock), 0, s, mask, bsum, words, (uint32_t)W, WW,
+                           base, out, cap, n_out);
+    } else {
+        hipLaunchKernelGGL(st_scan, dim3(1), dim3(1024), 0, s, bsum, nb);
+        hipLaunchKernelGGL(st_bases<false>, dim3(nb), dim3(kWordsPerBlock), 0, s, mask, bsum, words, (uint32_t)W, WW,
+                           base, out, cap, n_out);
+    }
+    hipLaunchKernelGGL(st_accum, dim3((WW + 1u) / 2u, ((uint32_t)H + kAccRows - 1u) / kAccRows), dim3(kAccWaves * 64),
                        0, s, labels,
                        (uint32_t)H, (uint32_t)W, WW, mask, base, out, cap);
     const hipError_t e = hipGetLastError();
