@@ -38,11 +38,13 @@ namespace ccl {
 // one after the other took 39.5.
 template <int TH>
 struct K1EqLds {
-    LineForest<TH, TH * 64, 16 * TH, 0> f;
+    static constexpr int JOINS = 32 * TH;
+    alignas(16) LineForest<TH, TH * 64, JOINS, 0> f;
     uint64_t S[TH];         // per row: run starts
     uint64_t flg[TH];       // per row: local roots of edge-touching components
-    alignas(16) uint8_t pix[TH * kTileW];  // the tile's bytes
     uint32_t nodes;
+    // the tile's bytes, in the joins' place until the masks are made
+    __device__ uint8_t *pix() { return (uint8_t *)f.join; }
 };
 
 // Kernel 1 body for tile t of image v, equal-value labeling.  Ends after a
@@ -71,7 +73,7 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int c = tid + i * NT;
-        if (c < CH) ((uint4 *)sh.pix)[c] = load_chunk(v, tx, ty, TH, c >> 2, c & 3);
+        if (c < CH) ((uint4 *)sh.pix())[c] = load_chunk(v, tx, ty, TH, c >> 2, c & 3);
     }
     if (tid < TH) flg[tid] = 0ull;
     if (tid == 0) F.joins = 0u;
@@ -85,7 +87,7 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
         const int c = tid + i * NT;
         if (c >= CH) break;
         const int r = c >> 2, q = c & 3;
-        const uint8_t *pr = sh.pix + r * kTileW + q * 16, *pu = pr - (r > 0 ? kTileW : 0);
+        const uint8_t *pr = sh.pix() + r * kTileW + q * 16, *pu = pr - (r > 0 ? kTileW : 0);
         const uint4 w = *(const uint4 *)pr, u = *(const uint4 *)pu;
         // the 16 bytes one column to the left / right (what lies beyond the
         // tile's columns is masked)
@@ -144,7 +146,7 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
     for (int i = tid; i < TH * 8; i += NT)
         if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
     __syncthreads();
-    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
+    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)K1EqLds<TH>::JOINS);
     if (joins) {  // workgroup-uniform
         compress_nodes<NT>(par, nodes, [](uint32_t) {});
         __syncthreads();
@@ -154,21 +156,21 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
         }
         __syncthreads();
     }
-    compress_nodes<NT>(par, nodes, [](uint32_t) {});
-    __syncthreads();
-    // records: the first pixel of the node's component
+    // records: the first pixel of the node's component, which is also left as
+    // the node's entry (a walk that meets it there has found what it looks for)
     uint16_t *sl = v.slots + (size_t)t * TH * SPR;
     for (int i = tid; i < TH * 8; i += NT) {
         const int r = i >> 3, q = i & 7;
         const uint32_t first = F.pre[i], base = F.base[r], e8 = ((const uint8_t *)F.E)[i];
         for (uint32_t s8 = (uint32_t)(sh.S[r] >> (8 * q)) & 0xFFu; s8; s8 &= s8 - 1u) {
             const uint32_t n = first + (uint32_t)__builtin_popcount(e8 & ((1u << __builtin_ctz(s8)) - 1u));
-            uint32_t e = lds_ld(&par[n]);
-            if (e < kPixel) {
-                e = lds_ld(&par[e]);
-                lds_st(&par[n], e);  // read below by edge cells; its own thread alone reads it before
+            uint32_t p = lds_ld(&par[n]);
+            if (p < kPixel) {
+                do p = lds_ld(&par[p]);
+                while (p < kPixel);
+                lds_st(&par[n], p);
             }
-            sl[r * SPR + (int)(n - base)] = (uint16_t)e;
+            sl[r * SPR + (int)(n - base)] = (uint16_t)p;
         }
     }
     __syncthreads();
