@@ -18,7 +18,7 @@
 //                the labels that fill much of it one at a time, from lane
 //                masks; what is left goes run by run (runs of equal labels in
 //                a row).  Both add to a hash table in LDS keyed by label per
-//                128 x 256 block, which is added to the records once per slot
+//                128 x 128 block, which is added to the records once per slot
 //                with global atomics.
 #include <hip/hip_runtime.h>
 
@@ -174,23 +174,23 @@ __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t W
     return base[w] + (uint32_t)__popcll(mask[w] & ((1ull << (rx & 63u)) - 1ull));
 }
 
-// Block of 128 x 256 pixels, a wavefront per 64 columns and 32 rows.  The hash
+// Block of 128 x 128 pixels, a wavefront per 64 columns and 16 rows.  The hash
 // table is keyed by label, so an addition needs no global read; the record
 // index is looked up once per table slot when the block flushes.  Bound by the
-// flushes of components that reach many blocks (atomics on one record follow
-// each other), hence few large blocks, about one per compute unit at 8
-// Mpixels, and a table for all the small components such a block may hold.
-// Gathering a label over a wavefront's strip makes its eight LDS additions
-// once per strip instead of once per row.  At most 80 scalar registers (eight
-// wavefronts per SIMD), so that two workgroups share a compute unit.
-// 2160 x 3840 smoothed labels: 27.6 us; adding run by run in blocks of 64 x 256
-// took 46.  Blocks of 128 x 128 took 33.4 (twice the flushes), eight
-// wavefronts per block 31.0.
-constexpr int kAccWaves = 16, kAccStripRows = 16, kAccStrips = 2;
-constexpr int kAccCols = 2 * kTileW, kAccRows = kAccWaves / 2 * kAccStripRows * kAccStrips;
-constexpr int kAccSlots = 2048;
-// Labels gathered over the strip at most (1, 2, 4 and 8 measured 28.1, 27.6,
-// 29.0 and 30.3 us), and the pixels a gathered label must have had for another
+// chain of LDS round trips in a wavefront and by the flushes of components
+// that reach many blocks (atomics on one record follow each other).  At most
+// 80 scalar registers (eight wavefronts per SIMD), so that two workgroups
+// share a compute unit; with 112 one ran at a time.  Gathering a label over a
+// wavefront's strip makes its eight LDS additions once per strip instead of
+// once per row.  2160 x 3840 smoothed labels: 46 us before, 35 so.  Blocks of
+// 128 x 256 take 28 there and 15 to 30 % less on large images of large
+// components, but up to 7 % more where components are many and small
+// (4-connectivity, p = 0.3), with half as many workgroups to share them.
+constexpr int kAccWaves = 16, kAccStripRows = 16;
+constexpr int kAccCols = 2 * kTileW, kAccRows = kAccWaves / 2 * kAccStripRows;
+constexpr int kAccSlots = 1024;
+// Labels gathered over the strip at most (with 256-row blocks 1, 2, 4 and 8
+// measured 28.1, 27.6, 29.0 and 30.3 us), and the pixels a gathered label must have had for another
 // one to be tried: a strip of small components is cheaper run by run.
 constexpr int kAccGather = 2;
 constexpr uint32_t kAccGatherPixels = 24u;
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
                                                           const uint32_t *base, ccl_component *out,
                                                           uint32_t cap) {
     // extents and sums relative to the block's first pixel (a sum is at most
-    // 2^15 * 255)
+    // 2^14 * 127)
     __shared__ uint32_t key[kAccSlots], area[kAccSlots], xmn[kAccSlots], ymn[kAccSlots],
         xmx[kAccSlots], ymx[kAccSlots], sx[kAccSlots], sy[kAccSlots];
     constexpr int NT = kAccWaves * 64;
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
     __syncthreads();
     const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * (uint32_t)kAccRows;
     const uint32_t xr = (uint32_t)(wave & 1) * kTileW;  // the wavefront's first column and row in the block
-    const uint32_t yr = (uint32_t)(wave >> 1) * (kAccStripRows * kAccStrips);
+    const uint32_t yw = (uint32_t)(wave >> 1) * kAccStripRows;
     const uint32_t n = H * W;
     const uint32_t x = bx + xr + (uint32_t)lane;
     const bool xin = x < W;
@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
     // Adds one run (or a strip's pixels of one label) to the LDS table.
     auto add_lds = [&](uint32_t l, uint32_t len, uint32_t xa, uint32_t xb, uint32_t ya, uint32_t yb,
                        uint32_t sxv, uint32_t syv) {
-        uint32_t h = (l * 2654435761u) >> 21;  // 11 bits
+        uint32_t h = (l * 2654435761u) >> 22;  // 10 bits
         for (int probe = 0; probe < 16; ++probe) {
             const uint32_t kk = atomicCAS(&key[h], kEmpty, l);
             if (kk == kEmpty || kk == l) {
@@ -248,62 +248,59 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
         // table full around h: straight to the record
         to_record(l, len, xa, xb, ya, yb, sxv, syv);
     };
+    // all the strip's rows are loaded first, so the loads overlap
+    uint32_t lv[kAccStripRows];
+#pragma unroll
+    for (int k = 0; k < kAccStripRows; ++k) {
+        const uint32_t y = by + yw + (uint32_t)k;
+        const uint32_t l = xin && y < H ? L[y * W + x] : 0u;
+        lv[k] = l <= n ? l : 0u;  // (labels above H*W: not canonical)
+    }
 #pragma unroll 1
-    for (uint32_t yw = yr; yw < yr + kAccStripRows * kAccStrips && by + yw < H; yw += kAccStripRows) {
-        // all the strip's rows are loaded first, so the loads overlap
-        uint32_t lv[kAccStripRows];
+    for (int g = 0; g < kAccGather; ++g) {
+        // a label still in the strip: the topmost one of the first column
+        // that has any
+        uint32_t c = 0u;
 #pragma unroll
-        for (int k = 0; k < kAccStripRows; ++k) {
-            const uint32_t y = by + yw + (uint32_t)k;
-            const uint32_t l = xin && y < H ? L[y * W + x] : 0u;
-            lv[k] = l <= n ? l : 0u;  // (labels above H*W: not canonical)
+        for (int k = kAccStripRows - 1; k >= 0; --k) c = lv[k] ? lv[k] : c;
+        const uint64_t any = __ballot(c != 0u);
+        if (!any) break;
+        const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)c, __builtin_ctzll(any));
+        // its pixels per column (lanes) and per row; they leave the strip
+        uint32_t cnt = 0u, area = 0u, sr = 0u, ymask = 0u;
+        uint64_t xmask = 0ull;
+#pragma unroll
+        for (int k = kAccStripRows - 1; k >= 0; --k) {
+            const bool is = lv[k] == l;
+            const uint64_t m = __ballot(is);
+            cnt += is ? 1u : 0u;
+            lv[k] = is ? 0u : lv[k];
+            xmask |= m;
+            ymask |= m ? 1u << k : 0u;
+            area += (uint32_t)__popcll(m);
+            if (k > 0) sr += area;  // the pixels of rows >= k, summed over k >= 1: every pixel's row
         }
-#pragma unroll 1
-        for (int g = 0; g < kAccGather; ++g) {
-            // a label still in the strip: the topmost one of the first column
-            // that has any
-            uint32_t c = 0u;
+        uint32_t sc;  // column sum, at most 16 * 2016
+        wave_exclusive_scan(cnt * (uint32_t)lane, &sc);
+        if (lane == 0)
+            add_lds(l, area, xr + (uint32_t)__builtin_ctzll(xmask), xr + 63u - (uint32_t)__builtin_clzll(xmask),
+                    yw + (uint32_t)__builtin_ctz(ymask), yw + 31u - (uint32_t)__builtin_clz(ymask),
+                    area * xr + sc, area * yw + sr);
+        if (area < kAccGatherPixels) break;
+    }
 #pragma unroll
-            for (int k = kAccStripRows - 1; k >= 0; --k) c = lv[k] ? lv[k] : c;
-            const uint64_t any = __ballot(c != 0u);
-            if (!any) break;
-            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)c, __builtin_ctzll(any));
-            // its pixels per column (lanes) and per row; they leave the strip
-            uint32_t cnt = 0u, area = 0u, sr = 0u, ymask = 0u;
-            uint64_t xmask = 0ull;
-#pragma unroll
-            for (int k = kAccStripRows - 1; k >= 0; --k) {
-                const bool is = lv[k] == l;
-                const uint64_t m = __ballot(is);
-                cnt += is ? 1u : 0u;
-                lv[k] = is ? 0u : lv[k];
-                xmask |= m;
-                ymask |= m ? 1u << k : 0u;
-                area += (uint32_t)__popcll(m);
-                if (k > 0) sr += area;  // the pixels of rows >= k, summed over k >= 1: every pixel's row
-            }
-            uint32_t sc;  // column sum, at most 16 * 2016
-            wave_exclusive_scan(cnt * (uint32_t)lane, &sc);
-            if (lane == 0)
-                add_lds(l, area, xr + (uint32_t)__builtin_ctzll(xmask), xr + 63u - (uint32_t)__builtin_clzll(xmask),
-                        yw + (uint32_t)__builtin_ctz(ymask), yw + 31u - (uint32_t)__builtin_clz(ymask),
-                        area * xr + sc, area * yw + sr);
-            if (area < kAccGatherPixels) break;
-        }
-#pragma unroll
-        for (int k = 0; k < kAccStripRows; ++k) {
-            const uint32_t y = yw + (uint32_t)k;
-            const uint32_t l = lv[k];
-            const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
-            const uint64_t E = __ballot(l != 0u && l != lr);
-            if (!E) continue;  // wave-uniform
-            if (l == 0u || l == ll) continue;
-            // this lane starts a run of equal labels; it ends at the first run
-            // end at or after it
-            const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
-            const uint32_t len = e - (uint32_t)lane + 1u, xa = xr + (uint32_t)lane, xb = xr + e;
-            add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
-        }
+    for (int k = 0; k < kAccStripRows; ++k) {
+        const uint32_t y = yw + (uint32_t)k;
+        const uint32_t l = lv[k];
+        const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
+        const uint64_t E = __ballot(l != 0u && l != lr);
+        if (!E) continue;  // wave-uniform
+        if (l == 0u || l == ll) continue;
+        // this lane starts a run of equal labels; it ends at the first run
+        // end at or after it
+        const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
+        const uint32_t len = e - (uint32_t)lane + 1u, xa = xr + (uint32_t)lane, xb = xr + e;
+        add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
     }
     __syncthreads();
     for (int i = tid; i < kAccSlots; i += NT) {
@@ -355,9 +352,8 @@ extern "C" int ccl_component_stats(const uint32_t *labels, int32_t H, int32_t W,
         hipLaunchKernelGGL(st_bases<false>, dim3(nb), dim3(kWordsPerBlock), 0, s, mask, bsum, words, (uint32_t)W, WW,
                            base, out, cap, n_out);
     }
-    hipLaunchKernelGGL(st_accum, dim3((WW + 1u) / 2u, ((uint32_t)H + kAccRows - 1u) / kAccRows), dim3(kAccWaves * 64),
-                       0, s, labels,
-                       (uint32_t)H, (uint32_t)W, WW, mask, base, out, cap);
+    hipLaunchKernelGGL(st_accum, dim3(((uint32_t)W + kAccCols - 1u) / kAccCols, ((uint32_t)H + kAccRows - 1u) / kAccRows),
+                       dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base, out, cap);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
