@@ -35,9 +35,13 @@ bool config_supported_equal(int th, int nw);
 hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t s,
                         hipEvent_t *ev = nullptr, bool equal = false);
 
-// The local merge and the boundary analysis of binary labeling for one
-// image on `s`, without the link.
-hipError_t launch_merge(const ImgView &v, int th, int nw, int conn, hipStream_t s);
+// The boundary analysis of binary labeling for one image on `s`, without the
+// other phases (tiles of at most 64 rows).
+hipError_t launch_boundary(const ImgView &v, int th, int conn, hipStream_t s);
+// The supported tile configurations of at most 64 rows (X(tile_h, waves)).
+#define CCL_FOR_EACH_LOW_CONFIG(X)                                                          \
+    X(16, 1) X(16, 2) X(16, 4) X(16, 8) X(32, 1) X(32, 2) X(32, 4) X(32, 8) X(32, 16) \
+        X(64, 1) X(64, 2) X(64, 4) X(64, 8) X(64, 16)
 
 // Workspace layout for one image: edge masks, edge-cell roots, row masks
 // (row foreground and edge-root masks), run slots.

@@ -26,6 +26,7 @@
 #include "ccl_device.h"
 #include "ccl_internal.h"
 #include "ccl_link.h"
+#include "ccl_merge.h"
 
 namespace ccl {
 
@@ -138,7 +139,6 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
     __syncthreads();
     // a root's entry is kPixel | its first pixel, the smallest of its
     // component (runs are numbered in raster order)
-    constexpr uint32_t kPixel = 0x80000000u;
     for (int i = tid; i < TH * 8; i += NT)
         forest_nodes(F, i >> 3, i & 7, sh.S[i >> 3],
                      [&](uint32_t, uint32_t c) { return kPixel | (uint32_t)((i >> 3) * kTileW) | c; });
@@ -219,195 +219,6 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
     }
     __syncthreads();  // every wavefront's marks are in
     if (tid < TH) rw[TH + tid] = flg[tid];
-    __syncthreads();  // LDS may be reused for another tile
-}
-
-// Binary local merge over two-row bands.
-template <int TH, bool CONN8>
-struct K1BandLds {
-    static constexpr int NB = TH / 2;
-    static constexpr int NODES = NB * (CONN8 ? 32 : 64);  // a band's most intervals
-    LineForest<NB, NODES, 16 * TH, NODES> f;
-    uint64_t msk[TH];  // per row: foreground mask
-    uint64_t flg[TH];  // per row: local roots of edge-touching components
-    uint32_t nodes;
-};
-
-// Kernel 1 body for tile t of image v, binary labeling.  Writes the tile's
-// row masks, edge-root masks, band interval ends and band bases, one record
-// per node (the tile-local pixel of its root), the edge masks and the roots
-// of the edge cells, and seeds those roots in the forest.  Ends after a
-// workgroup barrier.
-template <int TH, int NW, bool CONN8>
-__device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1BandLds<TH, CONN8> &sh) {
-    constexpr int NB = TH / 2;
-    constexpr int NT = NW * 64;
-    constexpr int CH = TH * 4;               // 16-byte chunks per tile
-    constexpr int LPT = (CH + NT - 1) / NT;  // chunks per thread
-    auto &F = sh.f;
-    uint32_t *par = F.par;
-    uint64_t *msk = sh.msk;
-    uint64_t *flg = sh.flg;
-    const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-    const uint32_t TX = (uint32_t)v.tilesX;
-    const int tx = (int)(t % TX), ty = (int)(t / TX);
-    const bool hasUp = ty > 0, hasDown = ty + 1 < v.tilesY;
-    const bool hasLeft = tx > 0, hasRight = tx + 1 < v.tilesX;
-
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-        const int c = tid + i * NT;
-        if (c < CH) ((uint16_t *)msk)[c] = (uint16_t)nonzero_bytes16(load_chunk(v, tx, ty, TH, c >> 2, c & 3));
-    }
-    for (int r = tid; r < TH; r += NT) flg[r] = 0ull;
-    __syncthreads();
-    // every band's intervals, one band per lane: nodes are numbered densely
-    // (an exclusive scan of the bands' interval counts)
-    if (wave == 0) {
-        const uint64_t bt = lane < NB ? msk[2 * lane] : 0ull, bb = lane < NB ? msk[2 * lane + 1] : 0ull;
-        const uint64_t s = band_starts<CONN8>(bt, bb);
-        uint32_t nodes;
-        const uint32_t b = wave_exclusive_scan((uint32_t)__popcll(s), &nodes);
-        if (lane < NB) {
-            F.E[lane] = band_ends(bt | bb, s);
-            F.base[lane] = (uint16_t)b;
-        }
-        if (lane == 0) {
-            sh.nodes = nodes;
-            F.joins = 0u;
-        }
-    }
-    __syncthreads();
-    // the touching pairs of every band with the band above, one band per
-    // lane (on a wavefront that did not scan)
-    if (wave == (NW > 1 ? 1 : 0) && lane < NB && lane > 0) {
-        const uint64_t t0 = msk[2 * lane], u = msk[2 * lane - 1];
-        const uint64_t M = t0 | msk[2 * lane + 1], Mu = u | msk[2 * lane - 2];
-        const uint64_t S = band_starts<CONN8>(t0, msk[2 * lane + 1]);
-        const uint64_t Su = band_starts<CONN8>(msk[2 * lane - 2], u);
-        const PairRequests q = pair_requests(t0 & u, CONN8 ? t0 & (u << 1) : 0ull, CONN8 ? t0 & (u >> 1) : 0ull, M, S,
-                                             F.E[lane], Mu, Su, F.E[lane - 1]);
-        F.f[lane] = q.f;
-        F.l[lane] = q.l;
-        F.r[lane] = q.r;
-    }
-    for (int i = tid; i < NB * 8; i += NT) {
-        const int k = i >> 3;
-        forest_nodes(F, k, i & 7, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]),
-                     [](uint32_t n, uint32_t) { return n; });
-    }
-    __syncthreads();
-    for (int i = tid; i < NB * 8; i += NT)
-        if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
-    __syncthreads();
-    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
-    if (joins) {  // workgroup-uniform
-        compress_nodes<NT>(par, nodes, [](uint32_t) {});
-        __syncthreads();
-        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
-            const uint32_t e = F.join[i];
-            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
-        }
-        __syncthreads();
-    }
-    // an interval's smallest pixel: its first top-row pixel, else its first
-    // pixel (a bottom-row one, at the start column)
-    auto smallest = [&](uint32_t n) {
-        const uint32_t in = F.info[n], k = in >> 6, s = in & 63u;
-        const uint64_t tr = msk[2 * k] >> s, er = F.E[k] >> s;
-        const uint32_t dt = tr ? (uint32_t)__builtin_ctzll(tr) : 64u;
-        const bool top = dt <= (uint32_t)__builtin_ctzll(er);
-        return ((2u * k + (top ? 0u : 1u)) << 6) | (s + (top ? dt : 0u));
-    };
-    // every node finds its root; a root's entry becomes kPixel | its smallest
-    // pixel, which walks still take for a root's (it is no smaller than any
-    // node)
-    constexpr uint32_t kPixel = 0x80000000u;
-    compress_nodes<NT>(par, nodes, [&](uint32_t n) { lds_st(&par[n], kPixel | smallest(n)); });
-    __syncthreads();
-    // a root without a top-row pixel: the component's smallest pixel may be
-    // the top-row pixel of another of its intervals in the band (once one
-    // has been entered, only of one that starts before it)
-    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
-        const uint32_t r = lds_ld(&par[n]);
-        if (r >= kPixel) continue;
-        const uint32_t e = lds_ld(&par[r]), in = F.info[n];
-        if ((in ^ (uint32_t)F.info[r]) >> 6 == 0u && ((e & 64u) || (in & 63u) < (e & 63u))) {
-            const uint32_t p = kPixel | smallest(n);
-            if (p < e) atomicMin(&par[r], p);
-        }
-    }
-    __syncthreads();
-    // records: the smallest pixel of the node's component
-    uint16_t *sl = v.slots + (size_t)t * TH * kSlotsPerRow;
-    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
-        uint32_t e = lds_ld(&par[n]);
-        if (e < kPixel) {
-            e = lds_ld(&par[e]);
-            lds_st(&par[n], e);
-        }
-        sl[n] = (uint16_t)e;
-    }
-    __syncthreads();
-    uint64_t *rw = v.rowmask + (size_t)t * rowmask_words(TH);
-    for (int r = tid; r < TH; r += NT) rw[r] = msk[r];
-    if (tid < NB) {
-        rw[rowmask_ends(TH) + tid] = F.E[tid];
-        ((uint16_t *)(rw + rowmask_bases(TH)))[tid] = F.base[tid];
-    }
-    // edge masks and edge-cell roots for the boundary analysis; every such
-    // root is seeded in the forest (lanes of one component store the same
-    // word) and marked in the edge-root masks.  The four edges go to four
-    // wavefronts (edge k to wavefront k mod NW), so their root loads and
-    // stores overlap.
-    {
-        uint64_t *mk = v.masks + (size_t)t * mask_words(TH);
-        uint32_t *rt = v.roots + (size_t)t * roots_per_tile(TH);
-        const uint64_t mTop = uniform64(msk[0]), mBot = uniform64(msk[TH - 1]);
-        auto root_g = [&](uint32_t n) {
-            const uint32_t pos = lds_ld(&par[n]) & (kPixel - 1u);
-            atomicOr((unsigned long long *)&flg[pos >> 6], 1ull << (pos & 63u));
-            return global_index(v, tx, ty, TH, pos);
-        };
-        auto put = [&](uint32_t *dst, uint32_t g) {
-            *dst = g;
-            v.labels[g] = g + 1u;
-        };
-        const uint32_t bbLast = (uint32_t)F.base[NB - 1];
-        if (wave == 0) {
-            if (hasUp && lane_in(mTop)) put(&rt[roots_top(TH) + lane], root_g(bits_below(uniform64(F.E[0]))));
-            if (lane == 0) {
-                mk[kMaskTop] = mTop;
-                mk[kMaskBottom] = mBot;
-            }
-        }
-        if (wave == 1 % NW && hasDown && lane_in(mBot))
-            put(&rt[roots_bottom(TH) + lane], root_g(bbLast + bits_below(uniform64(F.E[NB - 1]))));
-        // per row (lane = row, 64 rows at a time): the band's first / last
-        // interval holds the row's cell in the left / right column
-        if (wave == 2 % NW || wave == 3 % NW) {
-#pragma unroll
-            for (int h = 0; h < col_words(TH); ++h) {
-                const int r = 64 * h + lane;
-                const uint64_t mr = r < TH ? msk[r] : 0ull;
-                const bool lb = (mr & 1ull) != 0, rb = (mr >> 63) != 0;
-                const uint32_t bFirst = r < TH ? (uint32_t)F.base[r >> 1] : 0u;
-                const uint32_t nInt = r < TH ? (uint32_t)__popcll(F.E[r >> 1]) : 0u;
-                const uint64_t mLeft = __ballot(lb), mRight = __ballot(rb);
-                if (wave == 2 % NW) {
-                    if (hasLeft && lb) put(&rt[roots_left(TH) + r], root_g(bFirst));
-                    if (lane == 0) mk[kMaskLeft + h] = mLeft;
-                }
-                if (wave == 3 % NW) {
-                    if (hasRight && rb) put(&rt[roots_right(TH) + r], root_g(bFirst + nInt - 1u));
-                    if (lane == 0) mk[mask_right(TH) + h] = mRight;
-                }
-            }
-        }
-    }
-    __syncthreads();  // every wavefront's marks are in
-    for (int r = tid; r < TH; r += NT) rw[TH + r] = flg[r];
     __syncthreads();  // LDS may be reused for another tile
 }
 
@@ -563,7 +374,7 @@ __global__ void __launch_bounds__(NW * 64) k1_local_merge(ImgView v) {
         k1_tile_eq<TH, NW, CONN8>(v, t, sh);
     } else {
         __shared__ K1BandLds<TH, CONN8> sh;
-        k1_tile_bands<TH, NW, CONN8>(v, t, sh);
+        k1_tile_bands<TH, NW, CONN8>(v, t, sh, [] {});
     }
 }
 
@@ -618,7 +429,7 @@ __global__ void __launch_bounds__(NW * 64) k1_batch(BatchArgs a) {
     const uint32_t i = batch_image_of(a, g);
     if (threadIdx.x == 0) a.w.tile_img[g] = i;
     const BatchImage &d = a.descs[i];
-    k1_tile_bands<TH, NW, CONN8>(batch_view<TH>(d, a.w), g - d.tile_base, sh);
+    k1_tile_bands<TH, NW, CONN8>(batch_view<TH>(d, a.w), g - d.tile_base, sh, [] {});
 }
 
 template <int TH, bool CONN8>
@@ -658,12 +469,11 @@ static hipError_t launch_plain_t(const ImgView &v, hipStream_t stream, hipEvent_
     return hipGetLastError();
 }
 
-// Local merge and boundary analysis only (binary labeling): the phases
-// before a link kernel that the caller launches.
-template <int TH, int NW, bool CONN8>
-static hipError_t launch_merge_t(const ImgView &v, hipStream_t stream) {
+// Boundary analysis only (binary labeling), for callers with a local merge
+// and a link of their own.
+template <int TH, bool CONN8>
+static hipError_t launch_boundary_t(const ImgView &v, hipStream_t stream) {
     const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
-    hipLaunchKernelGGL((k1_local_merge<TH, NW, CONN8, false>), dim3(tiles), dim3(NW * 64), 0, stream, v);
     if (tiles > 1)
         hipLaunchKernelGGL((k2_boundary<TH, CONN8, false>), dim3((tiles + 3) / 4), dim3(256), 0, stream,
                            v, tiles);
@@ -691,9 +501,7 @@ bool config_supported(int th, int nw) {
     }
 }
 
-#define CCL_FOR_EACH_CONFIG(X)                                                              \
-    X(16, 1) X(16, 2) X(16, 4) X(16, 8) X(32, 1) X(32, 2) X(32, 4) X(32, 8) X(32, 16) \
-        X(64, 1) X(64, 2) X(64, 4) X(64, 8) X(64, 16) X(128, 2) X(128, 4) X(128, 8) X(128, 16)
+#define CCL_FOR_EACH_CONFIG(X) CCL_FOR_EACH_LOW_CONFIG(X) X(128, 2) X(128, 4) X(128, 8) X(128, 16)
 
 // Tile configurations compiled for equal-value labeling.
 #define CCL_FOR_EACH_EQ_CONFIG(X) X(16, 4) X(32, 2) X(32, 8) X(64, 4) X(64, 8)
@@ -726,13 +534,14 @@ hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_merge(const ImgView &v, int th, int nw, int conn, hipStream_t s) {
-#define CCL_CASE(T, N)                                                        \
-    if (th == T && nw == N)                                                   \
-        return conn == 8 ? launch_merge_t<T, N, true>(v, s) : launch_merge_t<T, N, false>(v, s);
-    CCL_FOR_EACH_CONFIG(CCL_CASE)
-#undef CCL_CASE
-    return hipErrorInvalidValue;
+hipError_t launch_boundary(const ImgView &v, int th, int conn, hipStream_t s) {
+    const bool c8 = conn == 8;
+    switch (th) {
+        case 16: return c8 ? launch_boundary_t<16, true>(v, s) : launch_boundary_t<16, false>(v, s);
+        case 32: return c8 ? launch_boundary_t<32, true>(v, s) : launch_boundary_t<32, false>(v, s);
+        case 64: return c8 ? launch_boundary_t<64, true>(v, s) : launch_boundary_t<64, false>(v, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 bool batch_kernels(int th, int nw, int conn, BatchKernels *out) {

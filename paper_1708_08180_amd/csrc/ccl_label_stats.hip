@@ -1,17 +1,20 @@
-// Labels and per-component statistics in one call: the link phase (Sec.
-// II-C) also gathers the size and location of every component (the
-// quantities the paper's introduction lists as the uses of the labels),
-// while it holds every band interval's final root in LDS, instead of a
-// second pass that reads the label image back.
+// Labels and per-component statistics in one call: the local merge (Sec.
+// II-A) also gathers the size and location of every local component (the
+// quantities the paper's introduction lists as the uses of the labels), while
+// it holds every band interval and its root in LDS, instead of a second pass
+// that reads the label image back.
 //
-//   local merge, boundary analysis   unchanged (binary labeling)
-//   k3_link_stats   the link for one tile.  Besides the labels it writes
-//                   one 16-byte record per local component (its final label
-//                   and tile-local statistics: pixel count, coordinate sums,
-//                   extent), gathered from the band intervals in LDS, and
-//                   per 64-pixel row word the mask of component roots (the
-//                   pixels whose label is their own index + 1) and of those
-//                   whose component reaches a shared tile edge.
+//   k1_merge_stats  the local merge for one tile.  Its nodes are the tile's
+//                   band intervals with their local roots, so it also gathers
+//                   one 16-byte record per local component (pixel count,
+//                   coordinate sums, extent) in LDS, and stores the masks of
+//                   local roots per 64-pixel row word.
+//   boundary analysis   unchanged (binary labeling)
+//   k3_link_stats   the link for one tile.  It adds the final labels of the
+//                   components that reach a shared tile edge to their
+//                   records, and reduces the root masks to component roots
+//                   (the pixels whose label is their own index + 1) and to
+//                   those whose component reaches a shared tile edge.
 //   st_band         per tile row (a few workgroups, each over a group of
 //                   tile columns): the rank of every row word's first
 //                   component root (components are numbered in raster order
@@ -29,6 +32,7 @@
 #include "ccl_device.h"
 #include "ccl_internal.h"
 #include "ccl_link.h"
+#include "ccl_merge.h"
 
 namespace ccl {
 
@@ -58,15 +62,6 @@ struct StatsView {
 // pixels high and wide, so every field fits.  Records of components inside
 // the tile fill the tile's slots from the front, the others from the back.
 
-// Wavefronts of the statistics link: 16 rows each, as in the plain link.
-// So that its scalar registers fit beside the statistics' own state, the
-// link keeps the band ends in a vector register and the local-id loop is
-// unrolled four rows at a time.
-template <int TH>
-constexpr int stats_waves() {
-    return TH / 16;
-}
-
 // Accumulators for this many local components at a time: a tile with more
 // local components takes several passes over its band intervals.
 constexpr int kStatsChunk = 256;
@@ -83,196 +78,182 @@ __device__ __forceinline__ uint32_t column_sum2(uint64_t a, uint64_t b) {
     return s;
 }
 
-template <int TH, bool CONN8>
-struct StatsLds {
-    static constexpr int NW = stats_waves<TH>();
-    static constexpr int RPW = TH / NW;
-    static constexpr int RMAX = stats_rmax(TH, CONN8);
-    // a wavefront's band intervals: at most 32 per band under
-    // 8-connectivity (runs), 64 under 4-connectivity
-    static constexpr int ILIST = RPW / 2 * (CONN8 ? 32 : 64);
-    uint32_t fin[TH * kTileW];
-    uint64_t rows[TH];                    // foreground per row
-    uint64_t frows[TH];                   // flagged local roots per row
-    uint64_t bends[TH / 2];               // band interval ends
-    uint64_t rmask[TH];                   // local roots per row
-    uint64_t fcm[TH];                     // flagged local roots that are component roots
-    uint32_t rpre[TH + 1];                // local roots in the rows above; [TH]: all
-    uint16_t rpos[RMAX];                  // local root pixel by local id; bit 15: flagged
-    uint32_t ilist[NW][ILIST];            // first column | last << 6 | band << 12 | root << 15
+template <int TH>
+struct K1StatsLds {
+    uint64_t rmask[TH];                    // local roots per row
+    uint32_t rpre[TH];                     // local roots in the rows above
     unsigned long long sums[kStatsChunk];  // packed count and sums (record layout)
     unsigned long long xm[kStatsChunk], ym[kStatsChunk];  // columns / rows holding pixels
-    uint32_t nrec[2], ncomp;
+    uint32_t nrec[2];
+};
+
+// Local merge with statistics.  The merge's own nodes are what the statistics
+// add up (one interval per thread, three LDS atomics each), so this adds the
+// accumulation alone to it.  When the link gathered them it listed the
+// intervals, the local roots and their numbers again for every tile, in 32 KB
+// of LDS: 63 us at 4096 x 4096, p = 0.5, 8-connectivity; now the
+// merge takes 43 us instead of 22 and the link 23 instead of 17.
+template <int TH, int NW, bool CONN8>
+__global__ void __launch_bounds__(NW * 64) k1_merge_stats(ImgView v, StatsView s) {
+    static_assert(TH <= 64, "one mask word per tile row and 6-bit row offsets");
+    constexpr uint32_t NT = NW * 64;
+    constexpr int RMAX = stats_rmax(TH, CONN8);
+    __shared__ K1BandLds<TH, CONN8> sh;
+    __shared__ K1StatsLds<TH> st;
+    const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = tid & 63u;
+    for (uint32_t r = tid; r < (uint32_t)TH; r += NT) st.rmask[r] = 0ull;
+    if (tid < 2u) st.nrec[tid] = 0u;
+    k1_tile_bands<TH, NW, CONN8>(v, t, sh, [&] {
+        auto &F = sh.f;
+        const uint32_t nodes = sh.nodes;
+        const uint32_t TX = (uint32_t)v.tilesX, W = (uint32_t)v.W;
+        const uint32_t tx = t % TX, ty = t / TX;
+        // local roots: a component's smallest pixel lies in the band of its
+        // root
+        for (uint32_t n = tid; n < nodes; n += NT) {
+            const uint32_t pos = lds_ld(&F.par[n]) & (kPixel - 1u);
+            if (pos >> 7 == (uint32_t)F.info[n] >> 6)
+                atomicOr((unsigned long long *)&st.rmask[pos >> 6], 1ull << (pos & 63u));
+        }
+        __syncthreads();
+        // numbered in raster order
+        uint32_t nroots;
+        const uint32_t pre = wave_exclusive_scan(lane < (uint32_t)TH ? (uint32_t)__popcll(st.rmask[lane]) : 0u, &nroots);
+        if (tid < (uint32_t)TH) {
+            st.rpre[tid] = pre;
+            const uint32_t y = ty * (uint32_t)TH + tid;
+            if (y < (uint32_t)v.H) s.cm[(size_t)y * TX + tx] = st.rmask[tid];
+        }
+        uint4 *rec = s.rec + (size_t)t * RMAX;
+        const uint32_t origin = ty * (uint32_t)TH * W + tx * (uint32_t)kTileW;
+        for (uint32_t c0 = 0; c0 < nroots; c0 += (uint32_t)kStatsChunk) {
+            for (uint32_t i = tid; i < (uint32_t)kStatsChunk; i += NT) {
+                st.sums[i] = 0ull;
+                st.xm[i] = 0ull;
+                st.ym[i] = 0ull;
+            }
+            __syncthreads();  // cleared; rpre written
+            // every interval adds its pixels to its local root's accumulators
+            for (uint32_t n = tid; n < nodes; n += NT) {
+                const uint32_t pos = lds_ld(&F.par[n]) & (kPixel - 1u);
+                const uint32_t rr = pos >> 6;
+                const uint32_t id = st.rpre[rr] + (uint32_t)__popcll(st.rmask[rr] & ((1ull << (pos & 63u)) - 1ull)) - c0;
+                if (id >= (uint32_t)kStatsChunk) continue;  // (before c0: wraps around)
+                const uint32_t in = F.info[n], k = in >> 6, c = in & 63u;
+                const uint32_t e = c + (uint32_t)__builtin_ctzll(F.E[k] >> c);
+                const uint32_t yt = 2u * k, yb = yt + 1u;
+                const uint64_t I = (~0ull >> (63u - e)) & (~0ull << c);
+                const uint64_t at = sh.msk[yt] & I, ab = sh.msk[yb] & I;
+                const uint32_t na = (uint32_t)__popcll(at), nb = (uint32_t)__popcll(ab);
+                const uint64_t sx = column_sum2(at, ab);
+                const uint64_t sy = yt * na + yb * nb;
+                const uint64_t packed = (uint64_t)(na + nb) | (sx << 13) | (sy << 31);
+                const uint64_t rows = (na ? 1ull << yt : 0ull) | (nb ? 1ull << yb : 0ull);
+                atomicAdd(&st.sums[id], (unsigned long long)packed);
+                // a large component's extent is soon whole, and lanes read
+                // one address together but change it one after the other
+                if (I & ~lds_ld(&st.xm[id])) atomicOr(&st.xm[id], (unsigned long long)I);
+                if (rows & ~lds_ld(&st.ym[id])) atomicOr(&st.ym[id], (unsigned long long)rows);
+            }
+            __syncthreads();
+            // one record per local component: those inside the tile from the
+            // front of the tile's slots, the others from the back; eight
+            // columns of a row per thread
+            for (uint32_t i = tid; i < (uint32_t)TH * 8u; i += NT) {
+                const uint32_t row = i >> 3, q = i & 7u;
+                const uint64_t m = st.rmask[row];
+                uint32_t m8 = (uint32_t)(m >> (8u * q)) & 0xFFu;
+                uint32_t id = m8 ? st.rpre[row] + (uint32_t)__popcll(m & ((1ull << (8u * q)) - 1ull)) - c0 : 0u;
+                for (; m8; m8 &= m8 - 1u, ++id) {
+                    if (id >= (uint32_t)kStatsChunk) continue;
+                    const uint32_t pos = (row << 6) | (8u * q + (uint32_t)__builtin_ctz(m8));
+                    const bool spanning = bit(sh.flg[row], (int)(pos & 63u)) != 0;
+                    const uint64_t su = st.sums[id], xm = st.xm[id], ym = st.ym[id];
+                    const uint32_t xa = (uint32_t)__builtin_ctzll(xm), xb = 63u - (uint32_t)__builtin_clzll(xm);
+                    const uint32_t ya = (uint32_t)__builtin_ctzll(ym), yb = 63u - (uint32_t)__builtin_clzll(ym);
+                    uint4 r;
+                    r.x = origin + row * W + (pos & 63u) + 1u;  // spanning: the link sets the final label
+                    r.y = ya | (yb << 6) | (pos << 12);
+                    r.z = (uint32_t)su;
+                    r.w = (uint32_t)(su >> 32) | (xa << 17) | (xb << 23);
+                    const uint32_t at = atomicAdd(&st.nrec[spanning ? 1 : 0], 1u);
+                    const uint32_t slot = spanning ? (uint32_t)(RMAX - 1) - at : at;
+                    if (slot < (uint32_t)RMAX) rec[slot] = r;  // always (at most RMAX local components)
+                }
+            }
+            __syncthreads();
+        }
+        if (tid == 0) s.ncnt[t] = st.nrec[0] | (st.nrec[1] << 16);
+    });
+}
+
+// Link with statistics: the plain link, then the records and root masks of
+// components that reach a shared tile edge.
+template <int TH>
+struct K3StatsLds {
+    uint32_t fin[TH * kTileW];
+    uint64_t fcm[TH];  // flagged local roots that are component roots
+    uint32_t ncomp;
 };
 
 template <int TH, bool CONN8>
-__global__ void __launch_bounds__(stats_waves<TH>() * 64) k3_link_stats(ImgView v, StatsView s) {
-    constexpr int NW = stats_waves<TH>(), NT = NW * 64;
+__global__ void __launch_bounds__(link_waves<TH>() * 64) k3_link_stats(ImgView v, StatsView s) {
+    constexpr int NW = link_waves<TH>();
+    constexpr uint32_t NT = NW * 64;
     using LR = LinkRows<TH, NW, false>;
-    constexpr int RPW = LR::RPW, BPW = LR::BPW;
-    using Lds = StatsLds<TH, CONN8>;
-    constexpr int RMAX = Lds::RMAX;
-    static_assert(TH <= 64, "one mask word per tile row and 6-bit row offsets");
-    __shared__ Lds sh;
+    constexpr int RPW = LR::RPW;
+    constexpr int RMAX = stats_rmax(TH, CONN8);
+    __shared__ K3StatsLds<TH> sh;
     const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
-    const int tid = (int)threadIdx.x;
+    const uint32_t tid = threadIdx.x;
     const uint64_t *rw = v.rowmask + (size_t)t * rowmask_words(TH);
-    // LDS copies of the tile's rows, flagged roots and band ends for the
-    // statistics (kept in scalar registers across the link as well, the
-    // masks of a wavefront's 16 rows would not fit)
-    if (tid < TH) {
-        sh.rows[tid] = rw[tid];
-        sh.frows[tid] = rw[TH + tid];
-        sh.fcm[tid] = 0ull;
-        if (tid < TH / 2) sh.bends[tid] = rw[rowmask_ends(TH) + tid];
-    }
-    if (tid == 0) {
-        sh.nrec[0] = 0u;
-        sh.nrec[1] = 0u;
-        sh.ncomp = 0u;
-    }
-    // accumulators of the first (usually only) chunk of local components
-    for (int i = tid; i < kStatsChunk; i += NT) {
-        sh.sums[i] = 0ull;
-        sh.xm[i] = 0ull;
-        sh.ym[i] = 0ull;
-    }
-    LR R;
-    k3_resolve<TH, NW, false, true>(v, t, rw, v.slots + (size_t)t * TH * kSlotsPerRow, sh.fin, R);
-    const int lane = tid & 63, wave = R.wave;
-    const uint32_t W = (uint32_t)v.W, TX = (uint32_t)v.tilesX;
-    const uint32_t tx = R.tx, ty = R.ty;
-    const uint32_t origin = ty * (uint32_t)TH * W + tx * (uint32_t)kTileW;
-    // the labels go out first
-    k3_write<TH, NW, false>(v, sh.fin, R);  // ends after a barrier
-    // flagged local roots that stayed roots of the forest are their
-    // component's root (unflagged local roots always are)
+    for (uint32_t r = tid; r < (uint32_t)TH; r += NT) sh.fcm[r] = 0ull;
+    if (tid == 0) sh.ncomp = 0u;
+    const uint32_t spanning = s.ncnt[t] >> 16;
+    uint32_t tx, ty;
     {
-        const uint64_t fv = lane < RPW ? sh.frows[wave * RPW + lane] : 0ull;
-        uint32_t nf;
-        const uint32_t fpre = wave_exclusive_scan((uint32_t)__popcll(fv), &nf);
-        for (uint32_t b = 0; b < nf; b += 64u) {  // wave-uniform
-            const uint32_t i = b + (uint32_t)lane;
-            const uint32_t l = (uint32_t)(wave * RPW * kTileW) + nth_flagged<RPW>(fv, fpre, i);
-            if (i < nf && sh.fin[l] == origin + (l >> 6) * W + (l & 63u)) atomicOr(&sh.fcm[l >> 6], 1ull << (l & 63u));
-        }
+        LR R;
+        k3_resolve<TH, NW, false>(v, t, rw, v.slots + (size_t)t * TH * kSlotsPerRow, sh.fin, R);
+        k3_write<TH, NW, false>(v, sh.fin, R);  // ends after a barrier
+        tx = R.tx;
+        ty = R.ty;
     }
-    // local roots: the pixels that are their own interval's root
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-        const uint32_t l = (uint32_t)((wave * RPW + k) * kTileW + lane);
-        const uint64_t rmk = __ballot(R.rec[k >> 1] == l);
-        if (lane == 0) sh.rmask[wave * RPW + k] = rmk;
-    }
-    // this wavefront's band intervals, listed densely: their first lane
-    // appends (first column, last column, band, root pixel)
-    uint32_t nint = 0;
-    uint32_t *il = sh.ilist[wave];
-#pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-        const int r0 = wave * RPW + 2 * i;
-        const uint64_t d = uniform64(sh.rows[r0]) | uniform64(sh.rows[r0 + 1]);
-        const uint64_t E = uniform64(sh.bends[wave * BPW + i]);
-        const uint64_t starts = d & ~((d & ~E) << 1);
-        if (lane_in(starts)) {
-            const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
-            il[nint + bits_below(starts)] = (uint32_t)lane | (e << 6) | ((uint32_t)i << 12) | (R.rec[i] << 15);
-        }
-        nint += (uint32_t)__popcll(starts);
+    const uint32_t lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t W = (uint32_t)v.W, TX = (uint32_t)v.tilesX;
+    const uint32_t origin = ty * (uint32_t)TH * W + tx * (uint32_t)kTileW;
+    // the records of components that reach an edge get their final labels;
+    // a flagged local root that stayed a root of the forest is its
+    // component's root (unflagged local roots always are)
+    uint4 *rec = s.rec + (size_t)t * RMAX;
+    for (uint32_t j = tid; j < spanning; j += NT) {
+        uint4 &r = rec[(uint32_t)(RMAX - 1) - j];
+        const uint32_t pos = (r.y >> 12) & 0xFFFu;
+        const uint32_t g = sh.fin[pos];
+        if (g == origin + (pos >> 6) * W + (pos & 63u))
+            atomicOr((unsigned long long *)&sh.fcm[pos >> 6], 1ull << (pos & 63u));
+        r.x = g + 1u;
     }
     __syncthreads();
-    // local roots in the rows above each row (lane = row), computed by every
-    // wavefront for itself
-    uint32_t nroots;
-    const uint32_t rpre_l = wave_exclusive_scan(lane < TH ? (uint32_t)__popcll(sh.rmask[lane]) : 0u, &nroots);
-    if (wave == 0) {
-        if (lane < TH) sh.rpre[lane] = rpre_l;
-        if (lane == 0) sh.rpre[TH] = nroots;
+    // component roots per row word, 16 rows per wavefront (lane = row)
+    uint32_t n = 0u;
+    if (lane < (uint32_t)RPW) {
+        const uint32_t row = wave * (uint32_t)RPW + lane, y = ty * (uint32_t)TH + row;
+        if (y < (uint32_t)v.H) {
+            const uint64_t flagged = rw[TH + row];
+            uint64_t &w = s.cm[(size_t)y * TX + tx];
+            const uint64_t cm = (w & ~flagged) | sh.fcm[row];
+            w = cm;
+            s.sm[(size_t)y * TX + tx] = cm & flagged;
+            n = (uint32_t)__popcll(cm);
+        }
     }
-    // local ids in raster order; component roots per row word
-    uint32_t ncomp = 0;
-#pragma unroll 4
-    for (int k = 0; k < RPW; ++k) {
-        const int row = wave * RPW + k;
-        const uint64_t rmk = uniform64(sh.rmask[row]), fk = uniform64(sh.frows[row]);
-        if (lane_in(rmk)) {
-            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)rpre_l, row) + bits_below(rmk);
-            sh.rpos[id] = (uint16_t)((uint32_t)(row * kTileW + lane) | (lane_in(fk) ? 0x8000u : 0u));
-        }
-        const uint64_t cmk = (rmk & ~fk) | uniform64(sh.fcm[row]);
-        const uint32_t y = ty * (uint32_t)TH + (uint32_t)row;
-        if (lane == 0 && y < (uint32_t)v.H) {
-            s.cm[(size_t)y * TX + tx] = cmk;
-            s.sm[(size_t)y * TX + tx] = cmk & fk;
-        }
-        ncomp += (uint32_t)__popcll(cmk);
-    }
-    if (lane == 0 && ncomp) atomicAdd(&sh.ncomp, ncomp);
-    uint4 *rec = s.rec + (size_t)t * RMAX;
-    for (uint32_t c0 = 0; c0 < nroots; c0 += (uint32_t)kStatsChunk) {
-        const uint32_t c1 = min(nroots, c0 + (uint32_t)kStatsChunk);
-        if (c0 > 0) {
-            for (uint32_t id = c0 + (uint32_t)tid; id < c1; id += NT) {
-                sh.sums[id - c0] = 0ull;
-                sh.xm[id - c0] = 0ull;
-                sh.ym[id - c0] = 0ull;
-            }
-        }
-        __syncthreads();  // accumulators cleared; rpre written
-        // every interval adds its pixels to its local root's accumulators
-        for (uint32_t j = (uint32_t)lane; j < nint; j += 64u) {
-            const uint32_t q = il[j];
-            const uint32_t c = q & 63u, e = (q >> 6) & 63u, i = (q >> 12) & 7u, r = q >> 15;
-            const uint32_t rr = r >> 6;
-            const uint32_t id = sh.rpre[rr] + (uint32_t)__popcll(sh.rmask[rr] & ((1ull << (r & 63u)) - 1ull));
-            if (id < c0 || id >= c1) continue;
-            const uint32_t yt = (uint32_t)(wave * RPW) + 2u * i, yb = yt + 1u;
-            const uint64_t I = (~0ull >> (63u - e)) & (~0ull << c);
-            const uint64_t at = sh.rows[yt] & I, ab = sh.rows[yb] & I;
-            const uint32_t na = (uint32_t)__popcll(at), nb = (uint32_t)__popcll(ab);
-            const uint64_t sx = column_sum2(at, ab);
-            const uint64_t sy = yt * na + yb * nb;
-            const uint64_t packed = (uint64_t)(na + nb) | (sx << 13) | (sy << 31);
-            const uint64_t rows = (na ? 1ull << yt : 0ull) | (nb ? 1ull << yb : 0ull);
-            atomicAdd(&sh.sums[id - c0], (unsigned long long)packed);
-            atomicOr(&sh.xm[id - c0], (unsigned long long)I);
-            atomicOr(&sh.ym[id - c0], (unsigned long long)rows);
-        }
-        __syncthreads();
-        // one record per local component: those inside the tile from the
-        // front of the tile's slots, the others from the back
-        for (uint32_t b0 = c0; b0 < c1; b0 += NT) {
-            const uint32_t id = b0 + (uint32_t)tid;
-            const bool has = id < c1;
-            const uint32_t p = has ? sh.rpos[id] : 0u;
-            const bool spanning = (p & 0x8000u) != 0;
-            const uint64_t mc = __ballot(has && !spanning), ms = __ballot(has && spanning);
-            uint32_t fc = 0, fs = 0;
-            if (lane == 0) {
-                if (mc) fc = atomicAdd(&sh.nrec[0], (uint32_t)__popcll(mc));
-                if (ms) fs = atomicAdd(&sh.nrec[1], (uint32_t)__popcll(ms));
-            }
-            fc = (uint32_t)__shfl((int)fc, 0, 64);
-            fs = (uint32_t)__shfl((int)fs, 0, 64);
-            if (!has) continue;
-            const uint32_t pos = p & 0x7FFFu;
-            const uint64_t su = sh.sums[id - c0], xm = sh.xm[id - c0], ym = sh.ym[id - c0];
-            const uint32_t x0 = (uint32_t)__builtin_ctzll(xm), x1 = 63u - (uint32_t)__builtin_clzll(xm);
-            const uint32_t y0 = (uint32_t)__builtin_ctzll(ym), y1 = 63u - (uint32_t)__builtin_clzll(ym);
-            uint4 r;
-            r.x = sh.fin[pos] + 1u;
-            r.y = y0 | (y1 << 6) | (pos << 12);
-            r.z = (uint32_t)su;
-            r.w = (uint32_t)(su >> 32) | (x0 << 17) | (x1 << 23);
-            const uint32_t slot = spanning ? (uint32_t)(RMAX - 1) - (fs + bits_below(ms)) : fc + bits_below(mc);
-            if (slot < (uint32_t)RMAX) rec[slot] = r;  // always (at most RMAX local components)
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        s.ncnt[t] = sh.nrec[0] | (sh.nrec[1] << 16);
-        s.tcnt[t] = sh.ncomp;
-    }
+    uint32_t total;
+    wave_exclusive_scan(n, &total);
+    if (lane == 0 && total) atomicAdd(&sh.ncomp, total);
+    __syncthreads();
+    if (tid == 0) s.tcnt[t] = sh.ncomp;
 }
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
@@ -607,12 +588,25 @@ template <int TH, bool CONN8>
 hipError_t launch_stats_t(const ImgView &v, const StatsView &s, hipStream_t st) {
     const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
     const uint32_t ng = ((uint32_t)v.tilesX + kBandGroupTiles - 1u) / kBandGroupTiles;
-    hipLaunchKernelGGL((k3_link_stats<TH, CONN8>), dim3(tiles), dim3(stats_waves<TH>() * 64), 0, st, v, s);
+    hipLaunchKernelGGL((k3_link_stats<TH, CONN8>), dim3(tiles), dim3(link_waves<TH>() * 64), 0, st, v, s);
     hipLaunchKernelGGL((st_band<TH, CONN8>), dim3((uint32_t)v.tilesY * ng), dim3(1024), 0, st, v, s);
     const uint32_t per = span_tiles<CONN8>((uint32_t)v.tilesX);
     hipLaunchKernelGGL((st_span<TH, CONN8>), dim3((uint32_t)v.tilesY * (((uint32_t)v.tilesX + per - 1u) / per)),
                        dim3(1024), 0, st, v, s);
     return hipGetLastError();
+}
+
+hipError_t launch_merge_stats(const ImgView &v, const StatsView &s, int th, int nw, int conn, hipStream_t st) {
+    const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
+#define CCL_CASE(T, N)                                                                              \
+    if (th == T && nw == N) {                                                                       \
+        if (conn == 8) hipLaunchKernelGGL((k1_merge_stats<T, N, true>), dim3(tiles), dim3(N * 64), 0, st, v, s); \
+        else hipLaunchKernelGGL((k1_merge_stats<T, N, false>), dim3(tiles), dim3(N * 64), 0, st, v, s);          \
+        return hipGetLastError();                                                                   \
+    }
+    CCL_FOR_EACH_LOW_CONFIG(CCL_CASE)
+#undef CCL_CASE
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_stats(const ImgView &v, const StatsView &s, int th, int conn, hipStream_t st) {
@@ -676,7 +670,8 @@ extern "C" int ccl_label_2d_stats(const uint8_t *img, int32_t H, int32_t W, int6
     s.out = out;
     s.n_out = n_out;
     s.cap = capacity > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)capacity;
-    hipError_t e = launch_merge(v, th, nw, connectivity, st);
+    hipError_t e = launch_merge_stats(v, s, th, nw, connectivity, st);
+    if (e == hipSuccess) e = launch_boundary(v, th, connectivity, st);
     if (e == hipSuccess) e = launch_stats(v, s, th, connectivity, st);
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
