@@ -99,7 +99,10 @@ int ccl_version(void);
  * wait.  ccl_shutdown releases it.  Calls on the same stream, from any
  * thread, are ordered by the stream; calls on different streams use
  * different workspaces.  Callers that must not allocate at all pass their
- * own workspace to ccl_label_2d_ex.
+ * own workspace to ccl_label_2d_ex.  Images of at most 256 lines (two rows of
+ * 64 columns: ceil(H/2) * ceil(W/64)) for which neither the caller nor the
+ * tuning table names a tile configuration are labeled in one launch that
+ * needs no workspace.
  * Returns CCL_OK or an error; on error nothing has been enqueued (except
  * CCL_ERR_HIP from a failed launch).
  */

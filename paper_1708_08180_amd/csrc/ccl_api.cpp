@@ -113,14 +113,15 @@ int validate_image(const void *img, int32_t H, int32_t W, int64_t pitch, const v
     return CCL_OK;
 }
 
-int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw) {
+int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw, bool *builtin) {
+    if (builtin) *builtin = false;
     if (cfg && (cfg->tile_h != 0 || cfg->waves != 0)) {
         if (!config_supported(cfg->tile_h, cfg->waves)) return CCL_ERR_UNSUPPORTED;
         *th = cfg->tile_h;
         *nw = cfg->waves;
         return CCL_OK;
     }
-    default_config(H, W, conn, th, nw);
+    default_config(H, W, conn, th, nw, builtin);
     return CCL_OK;
 }
 
@@ -192,7 +193,8 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
     if (rc != CCL_OK) return rc;
     if (connectivity != 4 && connectivity != 8) return CCL_ERR_UNSUPPORTED;
     int th = 0, nw = 0;
-    rc = resolve_config(H, W, connectivity, cfg, &th, &nw);
+    bool builtin = false;
+    rc = resolve_config(H, W, connectivity, cfg, &th, &nw, &builtin);
     if (rc != CCL_OK) return rc;
     const size_t need = ws_layout(H, W, th).total;
     hipStream_t s = (hipStream_t)stream;
@@ -201,7 +203,14 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
     if (ws) {
         if (workspace_bytes < need) return CCL_ERR_WORKSPACE;
         if (((uintptr_t)ws & 255u) != 0) return CCL_ERR_INVALID_ARG;
-    } else {
+    }
+    // small images that neither the caller nor the tuning table chose a
+    // configuration for are labeled in one launch, without a workspace
+    if (builtin && small_image(H, W)) {
+        const hipError_t e = launch_small(make_view(img, H, W, pitch, labels, nullptr, th), connectivity, s);
+        return e == hipSuccess ? CCL_OK : fail_hip(e);
+    }
+    if (!ws) {
         rc = stream_workspace(s, need, &ws, &held);
         if (rc != CCL_OK) return rc;
     }

@@ -619,14 +619,26 @@ __device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S, En
     }
 }
 
-// Hooks of columns [8 q, 8 q + 8) of line k >= 1.
+// Hook of node lo under node up, or a join of the node it was hooked under.
+template <int LINES, int NODES, int JOINS, int INFO>
+__device__ __forceinline__ void forest_hook(LineForest<LINES, NODES, JOINS, INFO> &sh, uint32_t lo, uint32_t up) {
+    const uint32_t old = atomicMin(&sh.par[lo], up);
+    if (old < lo && old != up) {
+        const uint32_t j = atomicAdd(&sh.joins, 1u);
+        if (j < (uint32_t)JOINS) sh.join[j] = old | (up << 16);
+        else lds_link(sh.par, old, up);
+    }
+}
+
+// Hooks of columns [8 q, 8 q + 8) of line k, whose line above is `above`
+// lines before it.
 template <bool DIAG, int LINES, int NODES, int JOINS, int INFO>
-__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS, INFO> &sh, int k, int q) {
-    const int i = k * 8 + q;
+__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS, INFO> &sh, int k, int q, int above = 1) {
+    const int i = k * 8 + q, iu = i - 8 * above;
     uint32_t m = ((const uint8_t *)sh.f)[i];
     if (DIAG) m |= ((uint32_t)((const uint8_t *)sh.l)[i] << 8) | ((uint32_t)((const uint8_t *)sh.r)[i] << 16);
-    const uint32_t e8 = ((const uint8_t *)sh.E)[i], u8 = ((const uint8_t *)sh.E)[i - 8];
-    const uint32_t first = sh.pre[i], ufirst = sh.pre[i - 8];
+    const uint32_t e8 = ((const uint8_t *)sh.E)[i], u8 = ((const uint8_t *)sh.E)[iu];
+    const uint32_t first = sh.pre[i], ufirst = sh.pre[iu];
     for (; m; m &= m - 1u) {
         const uint32_t p = (uint32_t)__builtin_ctz(m), b = p & 7u, below = (1u << b) - 1u;
         const uint32_t lo = first + (uint32_t)__builtin_popcount(e8 & below);
@@ -635,12 +647,7 @@ __device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS, INF
             if (p >= 16u) up += (u8 >> b) & 1u;  // the interval that starts right of b
             else if (p >= 8u) up -= 1u;          // the one that ends left of b
         }
-        const uint32_t old = atomicMin(&sh.par[lo], up);
-        if (old < lo && old != up) {
-            const uint32_t j = atomicAdd(&sh.joins, 1u);
-            if (j < (uint32_t)JOINS) sh.join[j] = old | (up << 16);
-            else lds_link(sh.par, old, up);
-        }
+        forest_hook(sh, lo, up);
     }
 }
 

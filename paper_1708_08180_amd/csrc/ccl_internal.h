@@ -35,6 +35,11 @@ bool config_supported_equal(int th, int nw);
 hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t s,
                         hipEvent_t *ev = nullptr, bool equal = false);
 
+// Images that label_small takes whole (binary labeling; one launch, no
+// workspace), and that launch.
+bool small_image(int H, int W);
+hipError_t launch_small(const ImgView &v, int conn, hipStream_t s);
+
 // The boundary analysis of binary labeling for one image on `s`, without the
 // other phases (tiles of at most 64 rows).
 hipError_t launch_boundary(const ImgView &v, int th, int conn, hipStream_t s);
@@ -86,8 +91,10 @@ int validate_image_only(const void *img, int32_t H, int32_t W, int64_t pitch);
 int validate_image(const void *img, int32_t H, int32_t W, int64_t pitch, const void *labels);
 // True when [a, a + na) and [b, b + nb) share a byte.
 bool byte_ranges_overlap(const void *a, unsigned __int128 na, const void *b, unsigned __int128 nb);
-int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw);
-void default_config(int H, int W, int conn, int *th, int *nw);
+// Tile configuration of a call: the caller's, else the tuning table's, else the
+// built-in one.  *builtin (may be null): neither chose one.
+int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw, bool *builtin = nullptr);
+void default_config(int H, int W, int conn, int *th, int *nw, bool *builtin = nullptr);
 // The kernels' view of one image whose workspace (ws_layout(H, W, th,
 // equal).total bytes, 256-byte aligned) starts at ws.
 ImgView make_view(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, uint32_t *labels,

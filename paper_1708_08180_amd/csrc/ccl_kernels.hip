@@ -397,6 +397,160 @@ __global__ void __launch_bounds__(NW * 64) k3_link(ImgView v) {
     k3_tile<TH, NW, EQ>(v, t, v.rowmask + (size_t)t * rowmask_words(TH), v.slots + (size_t)t * TH * SPR, fin);
 }
 
+// ------------------------------------------------------------- small images
+
+// A small image in one workgroup and one launch: the local merge's forest over
+// the whole image, whose lines are the 64-column words of its bands in raster
+// order, with joins between neighbouring words of a band; the labels are
+// written from LDS.  Such a call is bound by launches and by the latency of a
+// phase, not by work: 120 x 160 takes 16.8 us in three launches and 10.5 so.
+// The line lies where one compute unit's 16 wavefronts still keep up: at 192
+// lines of noise 14.5 us against 19.4, and the LDS of 256 lines of 64
+// intervals (4-connectivity) is 129 KB.
+constexpr int kSmallLines = 256;
+
+template <bool CONN8>
+struct SmallLds {
+    static constexpr int NODES = kSmallLines * (CONN8 ? 32 : 64);
+    static constexpr int JOINS = 4096;
+    LineForest<kSmallLines, NODES, JOINS, NODES> f;
+    uint64_t m[2][kSmallLines];  // top / bottom row masks of every line
+    uint32_t part[4], nodes;
+};
+
+template <bool CONN8>
+__global__ void __launch_bounds__(1024) label_small(ImgView v) {
+    constexpr int NT = 1024;
+    __shared__ SmallLds<CONN8> sh;
+    auto &F = sh.f;
+    uint32_t *par = F.par;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int WX = (v.W + kTileW - 1) / kTileW, NB = (v.H + 1) / 2, lines = NB * WX;
+    // line / WX for line < 256
+    const uint32_t inv = 65536u / (uint32_t)WX + 1u;
+    auto band_of = [&](uint32_t line) { return (line * inv) >> 16; };
+    for (int c = tid; c < lines * 8; c += NT) {
+        const int row = (c >> 2) & 1, q = c & 3;  // eight chunks per line
+        const uint32_t line = (uint32_t)c >> 3, k = band_of(line);
+        const int y = 2 * (int)k + row, x = (int)(line - k * (uint32_t)WX) * kTileW + q * 16;
+        uint32_t bits = 0u;
+        if (y < v.H) bits = nonzero_bytes16(load_row16(v.img + (int64_t)y * v.pitch, x, v.W));
+        ((uint16_t *)&sh.m[row][line])[q] = (uint16_t)bits;
+    }
+    if (tid == 0) F.joins = 0u;
+    __syncthreads();
+    // every line's intervals, and their numbering (a line per thread)
+    uint32_t ex = 0u;
+    if (wave < kSmallLines / 64) {
+        const bool in = tid < lines;
+        const uint64_t t0 = in ? sh.m[0][tid] : 0ull, b0 = in ? sh.m[1][tid] : 0ull;
+        const uint64_t S = band_starts<CONN8>(t0, b0);
+        uint32_t total;
+        ex = wave_exclusive_scan((uint32_t)__popcll(S), &total);
+        F.E[tid] = band_ends(t0 | b0, S);
+        if (lane == 0) sh.part[wave] = total;
+    }
+    __syncthreads();
+    if (wave < kSmallLines / 64) {
+        uint32_t before = 0u, all = 0u;
+#pragma unroll
+        for (int j = 0; j < kSmallLines / 64; ++j) {
+            before += j < wave ? sh.part[j] : 0u;
+            all += sh.part[j];
+        }
+        F.base[tid] = (uint16_t)(before + ex);
+        if (tid == 0) sh.nodes = all;
+        // touching pairs with the line above (the same word of the band
+        // above); its corner columns look into the words beside it
+        PairRequests p = {0ull, 0ull, 0ull};
+        if (tid >= WX && tid < lines) {
+            const int up = tid - WX;
+            const uint32_t w = (uint32_t)tid - band_of((uint32_t)tid) * (uint32_t)WX;
+            const uint64_t t0 = sh.m[0][tid], b0 = sh.m[1][tid], tu = sh.m[0][up], u = sh.m[1][up];
+            uint64_t l = 0ull, r = 0ull;
+            if (CONN8) {
+                l = t0 & ((u << 1) | (w > 0u ? sh.m[1][up - 1] >> 63 : 0ull));
+                r = t0 & ((u >> 1) | (w + 1u < (uint32_t)WX ? sh.m[1][up + 1] << 63 : 0ull));
+            }
+            p = pair_requests(t0 & u, l, r, t0 | b0, band_starts<CONN8>(t0, b0), F.E[tid], tu | u,
+                              band_starts<CONN8>(tu, u), F.E[up]);
+        }
+        F.f[tid] = p.f;
+        F.l[tid] = p.l;
+        F.r[tid] = p.r;
+    }
+    __syncthreads();
+    for (int i = tid; i < lines * 8; i += NT) {
+        const int k = i >> 3;
+        forest_nodes(F, k, i & 7, band_starts<CONN8>(sh.m[0][k], sh.m[1][k]), [](uint32_t n, uint32_t) { return n; });
+    }
+    __syncthreads();
+    for (int i = tid; i < lines * 8; i += NT) {
+        const int k = i >> 3;
+        if (k >= WX) forest_hooks<CONN8>(F, k, i & 7, WX);
+        if ((i & 7) == 0 && k > 0 && (uint32_t)k != band_of((uint32_t)k) * (uint32_t)WX) {
+            // the band goes on from the word before
+            const uint64_t t0 = sh.m[0][k], b0 = sh.m[1][k], tl = sh.m[0][k - 1] >> 63, bl = sh.m[1][k - 1] >> 63;
+            const bool on = CONN8 ? ((tl | bl) & (t0 | b0) & 1ull) != 0 : (((tl & t0) | (bl & b0)) & 1ull) != 0;
+            if (on) forest_hook(F, (uint32_t)F.base[k], (uint32_t)F.base[k] - 1u);
+        }
+    }
+    __syncthreads();
+    const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)SmallLds<CONN8>::JOINS);
+    if (joins) {  // workgroup-uniform
+        compress_nodes<NT>(par, nodes, [](uint32_t) {});
+        __syncthreads();
+        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
+            const uint32_t e = F.join[i];
+            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
+        }
+        __syncthreads();
+    }
+    // roots' entries become kPixel | smallest pixel, row << 14 | column (see
+    // k1_tile_bands)
+    constexpr uint32_t kRow = 1u << 14;
+    auto smallest = [&](uint32_t n) {
+        const uint32_t in = F.info[n], line = in >> 6, s = in & 63u, k = band_of(line);
+        const uint64_t tr = sh.m[0][line] >> s, er = F.E[line] >> s;
+        const uint32_t dt = tr ? (uint32_t)__builtin_ctzll(tr) : 64u;
+        const bool top = dt <= (uint32_t)__builtin_ctzll(er);
+        const uint32_t x = (line - k * (uint32_t)WX) * (uint32_t)kTileW + s + (top ? dt : 0u);
+        return (2u * k + (top ? 0u : 1u)) * kRow | x;
+    };
+    compress_nodes<NT>(par, nodes, [&](uint32_t n) { lds_st(&par[n], kPixel | smallest(n)); });
+    __syncthreads();
+    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
+        const uint32_t r = lds_ld(&par[n]);
+        if (r >= kPixel) continue;
+        // a root without a top-row pixel, and a node of the same band
+        const uint32_t e = lds_ld(&par[r]);
+        const uint32_t first = band_of((uint32_t)F.info[n] >> 6) * (uint32_t)WX;
+        if (r >= (uint32_t)F.base[first]) {
+            const uint32_t p = kPixel | smallest(n);
+            if (p < e) atomicMin(&par[r], p);
+        }
+    }
+    __syncthreads();
+    // labels, a line's two rows at a time
+    for (int k = wave; k < lines; k += NT / 64) {
+        const uint32_t band = band_of((uint32_t)k);
+        const uint32_t x = ((uint32_t)k - band * (uint32_t)WX) * (uint32_t)kTileW + (uint32_t)lane;
+        const uint64_t t0 = uniform64(sh.m[0][k]), b0 = uniform64(sh.m[1][k]);
+        uint32_t val = 0u;
+        if (lane_in(t0 | b0)) {
+            uint32_t e = lds_ld(&par[(uint32_t)F.base[k] + bits_below(uniform64(F.E[k]))]);
+            if (e < kPixel) e = lds_ld(&par[e]);
+            e -= kPixel;
+            val = (e / kRow) * (uint32_t)v.W + (e & (kRow - 1u)) + 1u;
+        }
+        if (x >= (uint32_t)v.W) continue;
+        uint32_t *out = v.labels + (size_t)(2u * band) * (uint32_t)v.W + x;
+        *out = lane_in(t0) ? val : 0u;
+        if (2 * (int)band + 1 < v.H) out[v.W] = lane_in(b0) ? val : 0u;
+    }
+}
+
 // ------------------------------------------------------------ batch kernels
 
 template <int TH>
@@ -532,6 +686,16 @@ hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t 
     CCL_FOR_EACH_CONFIG(CCL_CASE)
 #undef CCL_CASE
     return hipErrorInvalidValue;
+}
+
+bool small_image(int H, int W) {
+    return ((int64_t)H + 1) / 2 * (((int64_t)W + kTileW - 1) / kTileW) <= kSmallLines;
+}
+
+hipError_t launch_small(const ImgView &v, int conn, hipStream_t s) {
+    if (conn == 8) hipLaunchKernelGGL(label_small<true>, dim3(1), dim3(1024), 0, s, v);
+    else hipLaunchKernelGGL(label_small<false>, dim3(1), dim3(1024), 0, s, v);
+    return hipGetLastError();
 }
 
 hipError_t launch_boundary(const ImgView &v, int th, int conn, hipStream_t s) {

@@ -35,7 +35,8 @@ int size_class(int H, int W) {
 
 }  // namespace
 
-void default_config(int H, int W, int conn, int *th, int *nw) {
+void default_config(int H, int W, int conn, int *th, int *nw, bool *builtin) {
+    if (builtin) *builtin = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_table.find(std::make_pair(size_class(H, W), conn));
@@ -48,6 +49,7 @@ void default_config(int H, int W, int conn, int *th, int *nw) {
     // built-in choice (measured on MI355X over 320x240 .. 8192^2, noise and
     // smoothed masks, both connectivities): 32-row tiles while the grid is
     // small, 64-row tiles from about 4 Mpixels up, 4 wavefronts each
+    if (builtin) *builtin = true;
     if ((int64_t)H * W < ((int64_t)1 << 22)) {
         *th = 32;
         *nw = 4;
