@@ -589,8 +589,9 @@ __device__ __forceinline__ uint64_t band_ends(uint64_t m, uint64_t s) { return m
 // in one long chain; local merge, both on one card: 4096 x 4096 p = 0.5,
 // 8-connectivity 28.0 us with the sweep, 22.4 so; 8192 x 8192 smoothed 63 and
 // 47; serpentine 56 and 32; 3001 x 4099 4-connectivity 18.6 and 15.6.
-template <int LINES, int NODES, int JOINS, int INFO>
+template <int LINES, int NODES, int JOINS, int INFO, int COLS = 8>
 struct LineForest {
+    static constexpr int kCols = COLS, kParts = 64 / COLS;  // columns per thread, threads per line
     static constexpr bool kInfo = INFO > 0;
     uint32_t par[NODES];
     uint32_t join[JOINS];      // upper nodes of a join, 16 bits each
@@ -598,30 +599,36 @@ struct LineForest {
     uint64_t E[LINES];         // interval ends
     uint64_t f[LINES], l[LINES], r[LINES];  // touching pairs with the line above
     uint16_t base[LINES];      // first node of the line
-    uint16_t pre[LINES * 8];   // first node at or after every eighth column
+    uint16_t pre[LINES * 64 / COLS];  // first node at or after every part's first column
     uint32_t joins;
+    // columns [COLS q, COLS q + COLS) of line k's mask in m
+    __device__ static uint32_t part(const uint64_t *m, int k, int q) {
+        const uint32_t b = ((const uint8_t *)m)[k * 8 + q * COLS / 8];
+        return COLS == 8 ? b : (b >> (COLS * q & 7)) & ((1u << COLS) - 1u);
+    }
 };
 
-// First node at or after column 8 q of line k, and the nodes of its eight
-// columns' intervals, given the interval starts S: every node a root, with
-// the entry root_entry(node, its first column).
+// First node at or after the first column of part q of line k, and the nodes
+// of the intervals that start in the part (S: the line's interval starts):
+// every node a root, with the entry root_entry(node, its first column).
 template <class F, class Entry>
 __device__ __forceinline__ void forest_nodes(F &sh, int k, int q, uint64_t S, Entry &&root_entry) {
+    constexpr uint32_t C = F::kCols, kMask = (1u << C) - 1u;
     const uint64_t E = sh.E[k];
-    const uint32_t e8 = (uint32_t)(E >> (8 * q)) & 0xFFu;
-    const uint32_t first = (uint32_t)sh.base[k] + (uint32_t)__popcll(E & ((1ull << (8 * q)) - 1ull));
-    sh.pre[k * 8 + q] = (uint16_t)first;
-    for (uint32_t s8 = (uint32_t)(S >> (8 * q)) & 0xFFu; s8; s8 &= s8 - 1u) {
-        const uint32_t b = (uint32_t)__builtin_ctz(s8);
-        const uint32_t n = first + (uint32_t)__builtin_popcount(e8 & ((1u << b) - 1u));
-        if (F::kInfo) sh.info[n] = (uint16_t)(((uint32_t)k << 6) | ((uint32_t)q << 3) | b);
-        lds_st(&sh.par[n], root_entry(n, 8u * (uint32_t)q + b));
+    const uint32_t e = (uint32_t)(E >> (C * q)) & kMask;
+    const uint32_t first = (uint32_t)sh.base[k] + (uint32_t)__popcll(E & ((1ull << (C * q)) - 1ull));
+    sh.pre[k * F::kParts + q] = (uint16_t)first;
+    for (uint32_t s = (uint32_t)(S >> (C * q)) & kMask; s; s &= s - 1u) {
+        const uint32_t b = (uint32_t)__builtin_ctz(s);
+        const uint32_t n = first + (uint32_t)__builtin_popcount(e & ((1u << b) - 1u));
+        if (F::kInfo) sh.info[n] = (uint16_t)(((uint32_t)k << 6) | (C * (uint32_t)q + b));
+        lds_st(&sh.par[n], root_entry(n, C * (uint32_t)q + b));
     }
 }
 
 // Hook of node lo under node up, or a join of the node it was hooked under.
-template <int LINES, int NODES, int JOINS, int INFO>
-__device__ __forceinline__ void forest_hook(LineForest<LINES, NODES, JOINS, INFO> &sh, uint32_t lo, uint32_t up) {
+template <int LINES, int NODES, int JOINS, int INFO, int COLS>
+__device__ __forceinline__ void forest_hook(LineForest<LINES, NODES, JOINS, INFO, COLS> &sh, uint32_t lo, uint32_t up) {
     const uint32_t old = atomicMin(&sh.par[lo], up);
     if (old < lo && old != up) {
         const uint32_t j = atomicAdd(&sh.joins, 1u);
@@ -630,22 +637,21 @@ __device__ __forceinline__ void forest_hook(LineForest<LINES, NODES, JOINS, INFO
     }
 }
 
-// Hooks of columns [8 q, 8 q + 8) of line k, whose line above is `above`
-// lines before it.
-template <bool DIAG, int LINES, int NODES, int JOINS, int INFO>
-__device__ __forceinline__ void forest_hooks(LineForest<LINES, NODES, JOINS, INFO> &sh, int k, int q, int above = 1) {
-    const int i = k * 8 + q, iu = i - 8 * above;
-    uint32_t m = ((const uint8_t *)sh.f)[i];
-    if (DIAG) m |= ((uint32_t)((const uint8_t *)sh.l)[i] << 8) | ((uint32_t)((const uint8_t *)sh.r)[i] << 16);
-    const uint32_t e8 = ((const uint8_t *)sh.E)[i], u8 = ((const uint8_t *)sh.E)[iu];
-    const uint32_t first = sh.pre[i], ufirst = sh.pre[iu];
+// Hooks of part q of line k, whose line above is `above` lines before it.
+template <bool DIAG, class F>
+__device__ __forceinline__ void forest_hooks(F &sh, int k, int q, int above = 1) {
+    const int i = k * F::kParts + q, ku = k - above;
+    uint32_t m = F::part(sh.f, k, q);
+    if (DIAG) m |= (F::part(sh.l, k, q) << 8) | (F::part(sh.r, k, q) << 16);
+    const uint32_t e = F::part(sh.E, k, q), u = F::part(sh.E, ku, q);
+    const uint32_t first = sh.pre[i], ufirst = sh.pre[i - above * F::kParts];
     for (; m; m &= m - 1u) {
         const uint32_t p = (uint32_t)__builtin_ctz(m), b = p & 7u, below = (1u << b) - 1u;
-        const uint32_t lo = first + (uint32_t)__builtin_popcount(e8 & below);
-        uint32_t up = ufirst + (uint32_t)__builtin_popcount(u8 & below);
+        const uint32_t lo = first + (uint32_t)__builtin_popcount(e & below);
+        uint32_t up = ufirst + (uint32_t)__builtin_popcount(u & below);
         if (DIAG) {
-            if (p >= 16u) up += (u8 >> b) & 1u;  // the interval that starts right of b
-            else if (p >= 8u) up -= 1u;          // the one that ends left of b
+            if (p >= 16u) up += (u >> b) & 1u;  // the interval that starts right of b
+            else if (p >= 8u) up -= 1u;         // the one that ends left of b
         }
         forest_hook(sh, lo, up);
     }

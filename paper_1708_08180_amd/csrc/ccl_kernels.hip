@@ -373,7 +373,7 @@ __global__ void __launch_bounds__(NW * 64) k1_local_merge(ImgView v) {
         __shared__ K1EqLds<TH> sh;
         k1_tile_eq<TH, NW, CONN8>(v, t, sh);
     } else {
-        __shared__ K1BandLds<TH, CONN8> sh;
+        __shared__ K1BandLds<TH, NW, CONN8> sh;
         k1_tile_bands<TH, NW, CONN8>(v, t, sh, [] {});
     }
 }
@@ -577,7 +577,7 @@ __device__ __forceinline__ ImgView batch_view(const BatchImage &b, const BatchWs
 // sizes the grids for every call.
 template <int TH, int NW, bool CONN8>
 __global__ void __launch_bounds__(NW * 64) k1_batch(BatchArgs a) {
-    __shared__ K1BandLds<TH, CONN8> sh;
+    __shared__ K1BandLds<TH, NW, CONN8> sh;
     const uint32_t g = xcd_remap(blockIdx.x, gridDim.x);
     if (g >= a.tiles) return;  // workgroup-uniform
     const uint32_t i = batch_image_of(a, g);

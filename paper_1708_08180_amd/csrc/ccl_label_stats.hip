@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(NW * 64) k1_merge_stats(ImgView v, StatsView s
     static_assert(TH <= 64, "one mask word per tile row and 6-bit row offsets");
     constexpr uint32_t NT = NW * 64;
     constexpr int RMAX = stats_rmax(TH, CONN8);
-    __shared__ K1BandLds<TH, CONN8> sh;
+    __shared__ K1BandLds<TH, NW, CONN8> sh;
     __shared__ K1StatsLds<TH> st;
     const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t tid = threadIdx.x;

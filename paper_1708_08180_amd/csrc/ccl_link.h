@@ -220,11 +220,14 @@ __device__ __forceinline__ void k3_tile(const ImgView &v, uint32_t t, const uint
     k3_write<TH, NW, EQ>(v, fin, R);
 }
 
-// Waves per workgroup of the link kernel: 16 rows per wave whatever the
-// local merge uses (measured best at 32 and 64 rows per tile).
+// Waves per workgroup of the link kernel, whatever the local merge uses: 16
+// rows per wave, measured best where the grid fills the chip; 8 for the 32-row
+// tiles of images below 4 Mpixels, where a wavefront's own chain of loads
+// counts (480 x 640 noise, 8-connectivity: 21.3 us a call with 16 rows, 20.2
+// with 8; 1080 x 1920: 24.8 and 24.4).
 template <int TH>
 constexpr int link_waves() {
-    return TH / 16;
+    return TH == 32 ? 4 : TH / 16;
 }
 
 }  // namespace ccl

@@ -9,11 +9,12 @@ namespace ccl {
 constexpr uint32_t kPixel = 0x80000000u;  // entry of a settled node: kPixel | its root's tile-local pixel
 
 // Binary local merge over two-row bands.
-template <int TH, bool CONN8>
+template <int TH, int NW, bool CONN8>
 struct K1BandLds {
     static constexpr int NB = TH / 2;
     static constexpr int NODES = NB * (CONN8 ? 32 : 64);  // a band's most intervals
-    LineForest<NB, NODES, 16 * TH, NODES> f;
+    // eight columns of a band per thread, four where that leaves threads idle
+    LineForest<NB, NODES, 16 * TH, NODES, (NB * 8 >= NW * 64 ? 8 : 4)> f;
     uint64_t msk[TH];  // per row: foreground mask
     uint64_t flg[TH];  // per row: local roots of edge-touching components
     uint32_t nodes;
@@ -26,7 +27,7 @@ struct K1BandLds {
 // end, when every node's entry is kPixel | its root's pixel and the flag masks
 // are whole.  Ends after a workgroup barrier.
 template <int TH, int NW, bool CONN8, class Then>
-__device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1BandLds<TH, CONN8> &sh, Then &&then) {
+__device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1BandLds<TH, NW, CONN8> &sh, Then &&then) {
     constexpr int NB = TH / 2;
     constexpr int NT = NW * 64;
     constexpr int CH = TH * 4;               // 16-byte chunks per tile
@@ -79,14 +80,15 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
         F.l[lane] = q.l;
         F.r[lane] = q.r;
     }
-    for (int i = tid; i < NB * 8; i += NT) {
-        const int k = i >> 3;
-        forest_nodes(F, k, i & 7, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]),
+    using Forest = decltype(sh.f);
+    for (int i = tid; i < NB * Forest::kParts; i += NT) {
+        const int k = i / Forest::kParts;
+        forest_nodes(F, k, i % Forest::kParts, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]),
                      [](uint32_t n, uint32_t) { return n; });
     }
     __syncthreads();
-    for (int i = tid; i < NB * 8; i += NT)
-        if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
+    for (int i = tid; i < NB * Forest::kParts; i += NT)
+        if (i >= Forest::kParts) forest_hooks<CONN8>(F, i / Forest::kParts, i % Forest::kParts);
     __syncthreads();
     const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
     if (joins) {  // workgroup-uniform
