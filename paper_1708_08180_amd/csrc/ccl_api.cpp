@@ -215,7 +215,7 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
         if (rc != CCL_OK) return rc;
     }
     const ImgView v = make_view(img, H, W, pitch, labels, ws, th);
-    const hipError_t e = launch_plain(v, th, nw, connectivity, s);
+    const hipError_t e = launch_plain(v, th, builtin ? merge_waves(th, nw) : nw, connectivity, s);
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
 }

@@ -95,6 +95,13 @@ bool byte_ranges_overlap(const void *a, unsigned __int128 na, const void *b, uns
 // built-in one.  *builtin (may be null): neither chose one.
 int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw, bool *builtin = nullptr);
 void default_config(int H, int W, int conn, int *th, int *nw, bool *builtin = nullptr);
+// Wavefronts the local merge runs with where nobody chose a configuration (the
+// other phases and the workspace depend on the tile height alone): 8 for
+// 32-row tiles, whose images leave the chip idle, so that the loops over a
+// tile's nodes take one pass (4-connectivity noise: 480 x 640 16.6 us a call
+// with 8, 17.3 with 4; 1080 x 1920 20.3 and 20.6; 8-connectivity 1080 x 1920
+// 25.3 and 25.1).
+inline int merge_waves(int th, int nw) { return th == 32 && nw == 4 ? 8 : nw; }
 // The kernels' view of one image whose workspace (ws_layout(H, W, th,
 // equal).total bytes, 256-byte aligned) starts at ws.
 ImgView make_view(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, uint32_t *labels,
