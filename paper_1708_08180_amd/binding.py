@@ -6,6 +6,7 @@ If the library has not been built, every call raises ``CclError``.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import threading
@@ -170,8 +171,19 @@ def _torch():
 def _stream_handle(stream):
     torch = _torch()
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current device's current stream, without building a Stream
+        # object for it (0.1 against 3 us a call)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+_HERE = contextlib.nullcontext()
+
+
+def _on(device):
+    """Context with `device` current; nothing to do when it is already."""
+    torch = _torch()
+    return _HERE if torch.cuda.current_device() == device.index else torch.cuda.device(device)
 
 
 def _pitch(img) -> int:
@@ -213,7 +225,6 @@ def _check_out(out, img, shape=None):
 def label(img, conn: int = 8, out=None, config=None, stream=None, workspace=None):
     """Label a 2D uint8 device image; returns an int32 tensor holding the
     uint32 labels bit for bit (0 = background, else 1 + min raster index)."""
-    torch = _torch()
     _check_image(img)
     H, W = img.shape
     out = _check_out(out, img)
@@ -226,7 +237,7 @@ def label(img, conn: int = 8, out=None, config=None, stream=None, workspace=None
         if not workspace.is_cuda or workspace.device != img.device or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous device tensor on the input's device")
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_label_2d_ex(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                                  ws_ptr, ws_bytes, cfg, _stream_handle(stream))
     _check(rc, "ccl_label_2d_ex")
@@ -235,12 +246,11 @@ def label(img, conn: int = 8, out=None, config=None, stream=None, workspace=None
 
 def label_plain(img, conn: int = 8, out=None, stream=None):
     """The plain ccl_label_2d entry point (library-owned workspace, default tiles)."""
-    torch = _torch()
     _check_image(img)
     H, W = img.shape
     out = _check_out(out, img)
     lib = load_library()
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_label_2d(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                               _stream_handle(stream))
     _check(rc, "ccl_label_2d")
@@ -251,12 +261,11 @@ def label_noalloc(img, conn: int = 8, out=None, stream=None):
     """The ccl_label_2d_noalloc entry point: default tiles, workspace in the
     library's fixed device array (no allocation by the library).  Calls
     whose work overlaps on one device race on that array."""
-    torch = _torch()
     _check_image(img)
     H, W = img.shape
     out = _check_out(out, img)
     lib = load_library()
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_label_2d_noalloc(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                                       _stream_handle(stream))
     _check(rc, "ccl_label_2d_noalloc")
@@ -267,13 +276,12 @@ def label_equal(img, conn: int = 8, out=None, config=None, stream=None):
     """Equal-value labeling of a 2D uint8 CUDA tensor (every value class,
     background included): int32 tensor of 1 + the smallest raster index of
     each pixel's equal-valued component."""
-    torch = _torch()
     _check_image(img)
     H, W = img.shape
     out = _check_out(out, img)
     lib = load_library()
     cfg = ctypes.byref(Config(int(config[0]), int(config[1]))) if config else None
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_label_2d_equal(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                                     cfg, _stream_handle(stream))
     _check(rc, "ccl_label_2d_equal")
@@ -300,7 +308,7 @@ def component_stats(labels, capacity: int = None, stream=None):
     H, W = labels.shape
     lib = load_library()
     n_dev = torch.zeros(1, dtype=torch.int32, device=labels.device)
-    with torch.cuda.device(labels.device):
+    with _on(labels.device):
         if capacity is None:
             _check(lib.ccl_component_stats(labels.data_ptr(), H, W, None, 0, n_dev.data_ptr(),
                                            _stream_handle(stream)), "ccl_component_stats")
@@ -329,7 +337,7 @@ def label_stats(img, conn: int = 8, capacity: int = None, out=None, config=None,
     lib = load_library()
     cfg = ctypes.byref(Config(int(config[0]), int(config[1]))) if config else None
     n_dev = torch.zeros(1, dtype=torch.int32, device=img.device)
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         if capacity is None:
             _check(lib.ccl_label_2d_stats(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                                           None, 0, n_dev.data_ptr(), cfg, _stream_handle(stream)),
@@ -356,7 +364,7 @@ def label3d(vol, conn: int = 26, out=None, stream=None):
     pitch_y = vol.stride(1) if H > 1 else W
     pitch_z = vol.stride(0) if D > 1 else H * pitch_y
     lib = load_library()
-    with torch.cuda.device(vol.device):
+    with _on(vol.device):
         rc = lib.ccl_label_3d(vol.data_ptr(), D, H, W, pitch_y, pitch_z, int(conn), out.data_ptr(),
                               _stream_handle(stream))
     _check(rc, "ccl_label_3d")
@@ -365,14 +373,13 @@ def label3d(vol, conn: int = 26, out=None, stream=None):
 
 def label_timed(img, conn: int = 8, out=None, config=None, stream=None):
     """Label and return (labels, [ms_phase1, ms_phase2, ms_phase3]); blocks."""
-    torch = _torch()
     _check_image(img)
     H, W = img.shape
     out = _check_out(out, img)
     lib = load_library()
     cfg = ctypes.byref(Config(int(config[0]), int(config[1]))) if config else None
     ms = (ctypes.c_float * 3)()
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_label_2d_timed(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(),
                                     cfg, _stream_handle(stream), ms)
     _check(rc, "ccl_label_2d_timed")
@@ -484,7 +491,7 @@ def autotune(img, conn: int = 8, reps: int = 5, stream=None):
     best = Config(0, 0)
     ms = ctypes.c_float(0.0)
     lib = load_library()
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         rc = lib.ccl_autotune(img.data_ptr(), H, W, _pitch(img), int(conn), out.data_ptr(), int(reps),
                               _stream_handle(stream), ctypes.byref(best), ctypes.byref(ms))
     _check(rc, "ccl_autotune")
