@@ -189,34 +189,49 @@ __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t W
 constexpr int kAccWaves = 16, kAccStripRows = 16;
 constexpr int kAccCols = 2 * kTileW, kAccRows = kAccWaves / 2 * kAccStripRows;
 constexpr int kAccSlots = 1024;
+// A workgroup takes up to this many blocks below each other, as many as leave
+// two workgroups per compute unit (kAccGroups), and flushes when its table is
+// half full, or at the end: where components are few and large, as many
+// blocks share one flush.  4096 x 4096 p = 0.5, 8-connectivity: 115 us a call
+// with a flush per block, 82 so; 6000 x 7000 smoothed 108 us, against 227 with
+// the blocks of 64 columns.  With half the workgroups 2160 x 3840 smoothed
+// takes 42 us instead of 50, but dense small components lose 4 %.
+constexpr uint32_t kAccMaxBlocks = 8u, kAccGroups = 512u;
 // Labels gathered over the strip at most (with 256-row blocks 1, 2, 4 and 8
 // measured 28.1, 27.6, 29.0 and 30.3 us), and the pixels a gathered label must have had for another
 // one to be tried: a strip of small components is cheaper run by run.
 constexpr int kAccGather = 2;
 constexpr uint32_t kAccGatherPixels = 24u;
 
+// SEVERAL: more than one block per workgroup.
+template <bool SEVERAL>
 __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L, uint32_t H, uint32_t W,
                                                           uint32_t WW, const uint64_t *mask,
                                                           const uint32_t *base, ccl_component *out,
-                                                          uint32_t cap) {
-    // extents and sums relative to the block's first pixel (a sum is at most
-    // 2^14 * 127)
+                                                          uint32_t cap, uint32_t blocks) {
+    const uint32_t per = SEVERAL ? blocks : 1u;
+    // extents and sums relative to the first block's first pixel (a sum is at
+    // most 2^17 * 1023)
     __shared__ uint32_t key[kAccSlots], area[kAccSlots], xmn[kAccSlots], ymn[kAccSlots],
         xmx[kAccSlots], ymx[kAccSlots], sx[kAccSlots], sy[kAccSlots];
+    __shared__ uint32_t used;
     constexpr int NT = kAccWaves * 64;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int i = tid; i < kAccSlots; i += NT) {
-        key[i] = kEmpty;
-        area[i] = 0u;
-        xmn[i] = ymn[i] = 0xFFFFFFFFu;
-        xmx[i] = ymx[i] = 0u;
-        sx[i] = sy[i] = 0u;
-    }
+    auto clear = [&] {
+        for (int i = tid; i < kAccSlots; i += NT) {
+            key[i] = kEmpty;
+            area[i] = 0u;
+            xmn[i] = ymn[i] = 0xFFFFFFFFu;
+            xmx[i] = ymx[i] = 0u;
+            sx[i] = sy[i] = 0u;
+        }
+        if (tid == 0) used = 0u;
+    };
+    clear();
     __syncthreads();
-    const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * (uint32_t)kAccRows;
+    const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * (uint32_t)kAccRows * per;
     const uint32_t xr = (uint32_t)(wave & 1) * kTileW;  // the wavefront's first column and row in the block
-    const uint32_t yw = (uint32_t)(wave >> 1) * kAccStripRows;
     const uint32_t n = H * W;
     const uint32_t x = bx + xr + (uint32_t)lane;
     const bool xin = x < W;
@@ -234,6 +249,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
         for (int probe = 0; probe < 16; ++probe) {
             const uint32_t kk = atomicCAS(&key[h], kEmpty, l);
             if (kk == kEmpty || kk == l) {
+                if (SEVERAL && kk == kEmpty) atomicAdd(&used, 1u);
                 atomicAdd(&area[h], len);
                 atomicMin(&xmn[h], xa);
                 atomicMax(&xmx[h], xb);
@@ -248,65 +264,79 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
         // table full around h: straight to the record
         to_record(l, len, xa, xb, ya, yb, sxv, syv);
     };
-    // all the strip's rows are loaded first, so the loads overlap
-    uint32_t lv[kAccStripRows];
-#pragma unroll
-    for (int k = 0; k < kAccStripRows; ++k) {
-        const uint32_t y = by + yw + (uint32_t)k;
-        const uint32_t l = xin && y < H ? L[y * W + x] : 0u;
-        lv[k] = l <= n ? l : 0u;  // (labels above H*W: not canonical)
-    }
 #pragma unroll 1
-    for (int g = 0; g < kAccGather; ++g) {
-        // a label still in the strip: the topmost one of the first column
-        // that has any
-        uint32_t c = 0u;
+    for (uint32_t j = 0; j < per && by + j * kAccRows < H; ++j) {  // workgroup-uniform
+        const uint32_t yw = j * kAccRows + (uint32_t)(wave >> 1) * kAccStripRows;
+        // all the strip's rows are loaded first, so the loads overlap
+        uint32_t lv[kAccStripRows];
 #pragma unroll
-        for (int k = kAccStripRows - 1; k >= 0; --k) c = lv[k] ? lv[k] : c;
-        const uint64_t any = __ballot(c != 0u);
-        if (!any) break;
-        const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)c, __builtin_ctzll(any));
-        // its pixels per column (lanes) and per row; they leave the strip
-        uint32_t cnt = 0u, area = 0u, sr = 0u, ymask = 0u;
-        uint64_t xmask = 0ull;
-#pragma unroll
-        for (int k = kAccStripRows - 1; k >= 0; --k) {
-            const bool is = lv[k] == l;
-            const uint64_t m = __ballot(is);
-            cnt += is ? 1u : 0u;
-            lv[k] = is ? 0u : lv[k];
-            xmask |= m;
-            ymask |= m ? 1u << k : 0u;
-            area += (uint32_t)__popcll(m);
-            if (k > 0) sr += area;  // the pixels of rows >= k, summed over k >= 1: every pixel's row
+        for (int k = 0; k < kAccStripRows; ++k) {
+            const uint32_t y = by + yw + (uint32_t)k;
+            const uint32_t l = xin && y < H ? L[y * W + x] : 0u;
+            lv[k] = l <= n ? l : 0u;  // (labels above H*W: not canonical)
         }
-        uint32_t sc;  // column sum, at most 16 * 2016
-        wave_exclusive_scan(cnt * (uint32_t)lane, &sc);
-        if (lane == 0)
-            add_lds(l, area, xr + (uint32_t)__builtin_ctzll(xmask), xr + 63u - (uint32_t)__builtin_clzll(xmask),
-                    yw + (uint32_t)__builtin_ctz(ymask), yw + 31u - (uint32_t)__builtin_clz(ymask),
-                    area * xr + sc, area * yw + sr);
-        if (area < kAccGatherPixels) break;
-    }
+#pragma unroll 1
+        for (int g = 0; g < kAccGather; ++g) {
+            // a label still in the strip: the topmost one of the first column
+            // that has any
+            uint32_t c = 0u;
 #pragma unroll
-    for (int k = 0; k < kAccStripRows; ++k) {
-        const uint32_t y = yw + (uint32_t)k;
-        const uint32_t l = lv[k];
-        const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
-        const uint64_t E = __ballot(l != 0u && l != lr);
-        if (!E) continue;  // wave-uniform
-        if (l == 0u || l == ll) continue;
-        // this lane starts a run of equal labels; it ends at the first run
-        // end at or after it
-        const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
-        const uint32_t len = e - (uint32_t)lane + 1u, xa = xr + (uint32_t)lane, xb = xr + e;
-        add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
-    }
-    __syncthreads();
-    for (int i = tid; i < kAccSlots; i += NT) {
-        const uint32_t l = key[i];
-        if (l == kEmpty) continue;
-        to_record(l, area[i], xmn[i], xmx[i], ymn[i], ymx[i], sx[i], sy[i]);
+            for (int k = kAccStripRows - 1; k >= 0; --k) c = lv[k] ? lv[k] : c;
+            const uint64_t any = __ballot(c != 0u);
+            if (!any) break;
+            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)c, __builtin_ctzll(any));
+            // its pixels per column (lanes) and per row; they leave the strip
+            uint32_t cnt = 0u, area = 0u, sr = 0u, ymask = 0u;
+            uint64_t xmask = 0ull;
+#pragma unroll
+            for (int k = kAccStripRows - 1; k >= 0; --k) {
+                const bool is = lv[k] == l;
+                const uint64_t m = __ballot(is);
+                cnt += is ? 1u : 0u;
+                lv[k] = is ? 0u : lv[k];
+                xmask |= m;
+                ymask |= m ? 1u << k : 0u;
+                area += (uint32_t)__popcll(m);
+                if (k > 0) sr += area;  // the pixels of rows >= k, summed over k >= 1: every pixel's row
+            }
+            uint32_t sc;  // column sum, at most 16 * 2016
+            wave_exclusive_scan(cnt * (uint32_t)lane, &sc);
+            if (lane == 0)
+                add_lds(l, area, xr + (uint32_t)__builtin_ctzll(xmask), xr + 63u - (uint32_t)__builtin_clzll(xmask),
+                        yw + (uint32_t)__builtin_ctz(ymask), yw + 31u - (uint32_t)__builtin_clz(ymask),
+                        area * xr + sc, area * yw + sr);
+            if (area < kAccGatherPixels) break;
+        }
+#pragma unroll
+        for (int k = 0; k < kAccStripRows; ++k) {
+            const uint32_t y = yw + (uint32_t)k;
+            const uint32_t l = lv[k];
+            const uint32_t ll = from_left(l, 0u), lr = from_right(l, 0u);
+            const uint64_t E = __ballot(l != 0u && l != lr);
+            if (!E) continue;  // wave-uniform
+            if (l == 0u || l == ll) continue;
+            // this lane starts a run of equal labels; it ends at the first run
+            // end at or after it
+            const uint32_t e = (uint32_t)lane + (uint32_t)__builtin_ctzll(E >> lane);
+            const uint32_t len = e - (uint32_t)lane + 1u, xa = xr + (uint32_t)lane, xb = xr + e;
+            add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
+        }
+        __syncthreads();
+        const bool last = j + 1u == per || by + (j + 1u) * kAccRows >= H;
+        if (SEVERAL) {
+            const bool full = used > (uint32_t)kAccSlots / 2u;
+            __syncthreads();  // every wavefront has read it before the next block counts on
+            if (!last && !full) continue;
+        }
+        for (int i = tid; i < kAccSlots; i += NT) {
+            const uint32_t l = key[i];
+            if (l == kEmpty) continue;
+            to_record(l, area[i], xmn[i], xmx[i], ymn[i], ymx[i], sx[i], sy[i]);
+        }
+        if (!SEVERAL || last) break;
+        __syncthreads();
+        clear();
+        __syncthreads();
     }
 }
 
@@ -352,8 +382,15 @@ extern "C" int ccl_component_stats(const uint32_t *labels, int32_t H, int32_t W,
         hipLaunchKernelGGL(st_bases<false>, dim3(nb), dim3(kWordsPerBlock), 0, s, mask, bsum, words, (uint32_t)W, WW,
                            base, out, cap, n_out);
     }
-    hipLaunchKernelGGL(st_accum, dim3(((uint32_t)W + kAccCols - 1u) / kAccCols, ((uint32_t)H + kAccRows - 1u) / kAccRows),
-                       dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base, out, cap);
+    const uint32_t cols = ((uint32_t)W + kAccCols - 1u) / kAccCols, rows = ((uint32_t)H + kAccRows - 1u) / kAccRows;
+    const uint64_t per = min((uint64_t)kAccMaxBlocks, max((uint64_t)1, (uint64_t)cols * rows / kAccGroups));
+    const dim3 grid(cols, (rows + (uint32_t)per - 1u) / (uint32_t)per);
+    if (per > 1u)
+        hipLaunchKernelGGL(st_accum<true>, grid, dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base,
+                           out, cap, (uint32_t)per);
+    else
+        hipLaunchKernelGGL(st_accum<false>, grid, dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base,
+                           out, cap, 1u);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;

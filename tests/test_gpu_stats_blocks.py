@@ -49,3 +49,15 @@ def test_many_blocks():
     img[5::97, 3:60] = 1
     img[200::301, :] = 1
     _check(img, 8, "tall")
+
+
+@pytest.mark.parametrize("conn", [4, 8])
+def test_blocks_share_a_table(conn):
+    # workgroups of several blocks: one flush at the end (large components), a
+    # flush in between (many components), both in one column of blocks
+    H, W = 4097 + 128, 4096 + 70
+    img = np.zeros((H, W), np.uint8)
+    img[: H // 2] = wl.bernoulli(H // 2, W, 0.62, 8800)
+    img[H // 2:, ::2] = 1
+    img[H // 2 + 1::9] = 0
+    _check(img, conn, "several blocks")
