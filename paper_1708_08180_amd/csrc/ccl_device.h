@@ -183,19 +183,6 @@ __device__ __forceinline__ uint32_t g_min(uint32_t *p, uint32_t v) {
 // a root (p == x) and stops on anything that is not a valid parent; every
 // loop below therefore strictly decreases its index and always terminates.
 
-// Find without writes.  Compression is done by the owner of each node only
-// (see the finish pass of the local merge): a path-halving store by one
-// thread can land after another thread stored the final root into the same
-// node and leave a non-root ancestor there, which breaks every later reader
-// that takes par[n] to be the root.
-__device__ __forceinline__ uint32_t lds_root(const uint32_t *par, uint32_t x) {
-    while (true) {
-        const uint32_t p = lds_ld(&par[x]);
-        if (p >= x) return x;
-        x = p;
-    }
-}
-
 // Join the trees of a and b (Sec. II-A-3), the larger index under the
 // smaller, without finding the roots first: the atomicMin lowers the larger
 // node's parent to the smaller node and returns the parent it had.  If that
@@ -419,10 +406,6 @@ __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_in
 __device__ __forceinline__ uint32_t bits_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
-// acc + the set bits of m below this lane
-__device__ __forceinline__ uint32_t bits_below_plus(uint64_t m, uint32_t acc) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, acc));
-}
 
 // Value of lane-1 / lane+1 (whole-wave DPP shifts; lane 0 / 63 get `edge`).
 __device__ __forceinline__ uint32_t from_left(uint32_t v, uint32_t edge) {
@@ -431,18 +414,8 @@ __device__ __forceinline__ uint32_t from_left(uint32_t v, uint32_t edge) {
 __device__ __forceinline__ uint32_t from_right(uint32_t v, uint32_t edge) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x130, 0xF, 0xF, false);
 }
-// The same shifts for callers that never read lane 0's / lane 63's result:
-// those lanes get 0 (one instruction, no edge value to set up).
-__device__ __forceinline__ uint32_t from_left_any(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t from_right_any(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true);
-}
 
 __device__ __forceinline__ uint64_t run_starts(uint64_t d) { return d & ~(d << 1); }
-// last cell of every run
-__device__ __forceinline__ uint64_t run_ends(uint64_t d) { return d & ~(d >> 1); }
 
 // Exclusive prefix sum over the 64 lanes of a wavefront; *total gets the
 // sum of all lanes.  DPP row shifts scan each 16-lane row, then the last
