@@ -636,25 +636,32 @@ __device__ __forceinline__ uint32_t parent_of(const uint32_t *par, uint32_t n) {
     return p < n ? p : n;
 }
 
-// Points every node at its root and calls done(n) for the roots.  A node's
+// Points every node at its root and calls done(n) for the roots and then(n,
+// root, the root's entry as it was read) for the others.  A node's
 // owner alone stores to it, always an ancestor, and a walk stops on any entry
 // that is no smaller than its node.  (Two walks at a time per thread, to
 // overlap their loads, measured slower: the kernel is short of issue slots.)
-template <int NT, class Done>
-__device__ __forceinline__ void compress_nodes(uint32_t *par, uint32_t nodes, Done &&done) {
+template <int NT, class Done, class Then>
+__device__ __forceinline__ void compress_nodes(uint32_t *par, uint32_t nodes, Done &&done, Then &&then) {
     for (uint32_t n = threadIdx.x; n < nodes; n += NT) {
         uint32_t p = lds_ld(&par[n]);
         if (p >= n) {
             done(n);
             continue;
         }
+        uint32_t g;
         while (true) {
-            const uint32_t g = lds_ld(&par[p]);
+            g = lds_ld(&par[p]);
             if (g >= p) break;
             p = g;
             lds_st(&par[n], p);
         }
+        then(n, p, g);
     }
+}
+template <int NT, class Done>
+__device__ __forceinline__ void compress_nodes(uint32_t *par, uint32_t nodes, Done &&done) {
+    compress_nodes<NT>(par, nodes, done, [](uint32_t, uint32_t, uint32_t) {});
 }
 
 }  // namespace ccl

@@ -498,15 +498,6 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
     }
     __syncthreads();
     const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)SmallLds<CONN8>::JOINS);
-    if (joins) {  // workgroup-uniform
-        compress_nodes<NT>(par, nodes, [](uint32_t) {});
-        __syncthreads();
-        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
-            const uint32_t e = F.join[i];
-            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
-        }
-        __syncthreads();
-    }
     // roots' entries become kPixel | smallest pixel, row << 14 | column (see
     // k1_tile_bands)
     constexpr uint32_t kRow = 1u << 14;
@@ -520,17 +511,21 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
     };
     compress_nodes<NT>(par, nodes, [&](uint32_t n) { lds_st(&par[n], kPixel | smallest(n)); });
     __syncthreads();
-    for (uint32_t n = (uint32_t)tid; n < nodes; n += NT) {
-        const uint32_t r = lds_ld(&par[n]);
-        if (r >= kPixel) continue;
+    if (joins) {  // workgroup-uniform
+        for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
+            const uint32_t e = F.join[i];
+            lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));
+        }
+        __syncthreads();
+    }
+    compress_nodes<NT>(par, nodes, [](uint32_t) {}, [&](uint32_t n, uint32_t r, uint32_t e) {
         // a root without a top-row pixel, and a node of the same band
-        const uint32_t e = lds_ld(&par[r]);
         const uint32_t first = band_of((uint32_t)F.info[n] >> 6) * (uint32_t)WX;
         if (r >= (uint32_t)F.base[first]) {
             const uint32_t p = kPixel | smallest(n);
             if (p < e) atomicMin(&par[r], p);
         }
-    }
+    });
     __syncthreads();
     // labels, a line's two rows at a time
     for (int k = wave; k < lines; k += NT / 64) {
