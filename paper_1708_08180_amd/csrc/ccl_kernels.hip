@@ -413,7 +413,7 @@ template <bool CONN8>
 struct SmallLds {
     static constexpr int NODES = kSmallLines * (CONN8 ? 32 : 64);
     static constexpr int JOINS = 4096;
-    LineForest<kSmallLines, NODES, JOINS, NODES> f;
+    alignas(16) LineForest<kSmallLines, NODES, JOINS, NODES> f;
     uint64_t m[2][kSmallLines];  // top / bottom row masks of every line
     uint32_t part[4], nodes;
 };
@@ -430,6 +430,7 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
     // line / WX for line < 256
     const uint32_t inv = 65536u / (uint32_t)WX + 1u;
     auto band_of = [&](uint32_t line) { return (line * inv) >> 16; };
+    forest_roots<NT>(par, lines * (CONN8 ? 32 : 64));
     for (int c = tid; c < lines * 8; c += NT) {
         const int row = (c >> 2) & 1, q = c & 3;  // eight chunks per line
         const uint32_t line = (uint32_t)c >> 3, k = band_of(line);
@@ -483,12 +484,7 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
     __syncthreads();
     for (int i = tid; i < lines * 8; i += NT) {
         const int k = i >> 3;
-        forest_nodes(F, k, i & 7, band_starts<CONN8>(sh.m[0][k], sh.m[1][k]), [](uint32_t n, uint32_t) { return n; });
-    }
-    __syncthreads();
-    for (int i = tid; i < lines * 8; i += NT) {
-        const int k = i >> 3;
-        if (k >= WX) forest_hooks<CONN8>(F, k, i & 7, WX);
+        forest_line<CONN8>(F, k, i & 7, band_starts<CONN8>(sh.m[0][k], sh.m[1][k]), k >= WX ? WX : 0);
         if ((i & 7) == 0 && k > 0 && (uint32_t)k != band_of((uint32_t)k) * (uint32_t)WX) {
             // the band goes on from the word before
             const uint64_t t0 = sh.m[0][k], b0 = sh.m[1][k], tl = sh.m[0][k - 1] >> 63, bl = sh.m[1][k - 1] >> 63;

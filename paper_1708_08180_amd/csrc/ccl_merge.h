@@ -14,7 +14,7 @@ struct K1BandLds {
     static constexpr int NB = TH / 2;
     static constexpr int NODES = NB * (CONN8 ? 32 : 64);  // a band's most intervals
     // eight columns of a band per thread, four where that leaves threads idle
-    LineForest<NB, NODES, 16 * TH, NODES, (NB * 8 >= NW * 64 ? 8 : 4)> f;
+    alignas(16) LineForest<NB, NODES, 16 * TH, NODES, (NB * 8 >= NW * 64 ? 8 : 4)> f;
     uint64_t msk[TH];  // per row: foreground mask
     uint64_t flg[TH];  // per row: local roots of edge-touching components
     uint32_t nodes;
@@ -43,12 +43,20 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
     const bool hasUp = ty > 0, hasDown = ty + 1 < v.tilesY;
     const bool hasLeft = tx > 0, hasRight = tx + 1 < v.tilesX;
 
+    uint4 px[LPT];
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int c = tid + i * NT;
-        if (c < CH) ((uint16_t *)msk)[c] = (uint16_t)nonzero_bytes16(load_chunk(v, tx, ty, TH, c >> 2, c & 3));
+        px[i] = c < CH ? load_chunk(v, tx, ty, TH, c >> 2, c & 3) : make_uint4(0u, 0u, 0u, 0u);
     }
+    forest_roots<NT>(par, K1BandLds<TH, NW, CONN8>::NODES);  // while the pixels are on their way
     for (int r = tid; r < TH; r += NT) flg[r] = 0ull;
+    if (tid == 0) F.joins = 0u;
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int c = tid + i * NT;
+        if (c < CH) ((uint16_t *)msk)[c] = (uint16_t)nonzero_bytes16(px[i]);
+    }
     __syncthreads();
     // every band's intervals, one band per lane: nodes are numbered densely
     // (an exclusive scan of the bands' interval counts)
@@ -61,34 +69,27 @@ __device__ __forceinline__ void k1_tile_bands(const ImgView &v, uint32_t t, K1Ba
             F.E[lane] = band_ends(bt | bb, s);
             F.base[lane] = (uint16_t)b;
         }
-        if (lane == 0) {
-            sh.nodes = nodes;
-            F.joins = 0u;
-        }
+        if (lane == 0) sh.nodes = nodes;
     }
-    __syncthreads();
     // the touching pairs of every band with the band above, one band per
-    // lane (on a wavefront that did not scan)
+    // lane (on a wavefront that does not scan)
     if (wave == (NW > 1 ? 1 : 0) && lane < NB && lane > 0) {
         const uint64_t t0 = msk[2 * lane], u = msk[2 * lane - 1];
         const uint64_t M = t0 | msk[2 * lane + 1], Mu = u | msk[2 * lane - 2];
         const uint64_t S = band_starts<CONN8>(t0, msk[2 * lane + 1]);
         const uint64_t Su = band_starts<CONN8>(msk[2 * lane - 2], u);
         const PairRequests q = pair_requests(t0 & u, CONN8 ? t0 & (u << 1) : 0ull, CONN8 ? t0 & (u >> 1) : 0ull, M, S,
-                                             F.E[lane], Mu, Su, F.E[lane - 1]);
+                                             band_ends(M, S), Mu, Su, band_ends(Mu, Su));
         F.f[lane] = q.f;
         F.l[lane] = q.l;
         F.r[lane] = q.r;
     }
+    __syncthreads();
     using Forest = decltype(sh.f);
     for (int i = tid; i < NB * Forest::kParts; i += NT) {
         const int k = i / Forest::kParts;
-        forest_nodes(F, k, i % Forest::kParts, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]),
-                     [](uint32_t n, uint32_t) { return n; });
+        forest_line<CONN8>(F, k, i % Forest::kParts, band_starts<CONN8>(msk[2 * k], msk[2 * k + 1]), k > 0 ? 1 : 0);
     }
-    __syncthreads();
-    for (int i = tid; i < NB * Forest::kParts; i += NT)
-        if (i >= Forest::kParts) forest_hooks<CONN8>(F, i / Forest::kParts, i % Forest::kParts);
     __syncthreads();
     const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)(16 * TH));
     // an interval's smallest pixel: its first top-row pixel, else its first
