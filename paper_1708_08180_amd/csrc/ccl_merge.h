@@ -6,7 +6,8 @@
 
 namespace ccl {
 
-constexpr uint32_t kPixel = 0x80000000u;  // entry of a settled node: kPixel | its root's tile-local pixel
+// Entry of a settled node: kPixel | its root's tile-local pixel (3D: voxel).
+constexpr uint32_t kPixel = 0x80000000u;
 
 // Binary local merge over two-row bands.
 template <int TH, int NW, bool CONN8>
