@@ -560,8 +560,8 @@ __device__ __forceinline__ uint64_t band_ends(uint64_t m, uint64_t s) { return m
 // trips between its barriers.  A wavefront that swept its bands one after the
 // other, carrying each column's root in a register, issued more instructions
 // in one long chain; local merge, both on one card: 4096 x 4096 p = 0.5,
-// 8-connectivity 28.0 us with the sweep, 22.4 so; 8192 x 8192 smoothed 63 and
-// 47; serpentine 56 and 32; 3001 x 4099 4-connectivity 18.6 and 15.6.
+// 8-connectivity 27.0 us with the sweep, 20.0 so, 4-connectivity 23.2 and 21.3;
+// 8192 x 8192 smoothed 64 and 41; serpentine 56 and 30.
 template <int LINES, int NODES, int JOINS, int INFO, int COLS = 8>
 struct LineForest {
     static constexpr int kCols = COLS, kParts = 64 / COLS;  // columns per thread, threads per line

@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(NW * 64) k3_link(ImgView v) {
 // the whole image, whose lines are the 64-column words of its bands in raster
 // order, with joins between neighbouring words of a band; the labels are
 // written from LDS.  Such a call is bound by launches and by the latency of a
-// phase, not by work: 120 x 160 takes 16.8 us in three launches and 10.5 so.
+// phase, not by work: 120 x 160 takes 16.6 us in three launches and 9.5 so.
 // The line lies where one compute unit's 16 wavefronts still keep up: at 192
 // lines of noise 14.5 us against 19.4, and the LDS of 256 lines of 64
 // intervals (4-connectivity) is 129 KB.

@@ -126,7 +126,7 @@ struct K1Lds3d {
 // hooks the later interval under the earlier one; where the interval was
 // hooked before, the two upper intervals are listed, and joined after all
 // hooks have been compressed to trees of depth one, so that the walks are
-// short.  256^3 voxels at p = 0.3, 26-connectivity: 24 us; the wavefront per
+// short.  256^3 voxels at p = 0.3, 26-connectivity: 23 us; the wavefront per
 // slice that swept its rows one after the other and then joined each row with
 // six neighbour rows took 172.
 template <int CONN>

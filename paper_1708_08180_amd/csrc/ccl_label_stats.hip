@@ -92,7 +92,7 @@ struct K1StatsLds {
 // accumulation alone to it.  When the link gathered them it listed the
 // intervals, the local roots and their numbers again for every tile, in 32 KB
 // of LDS: 63 us at 4096 x 4096, p = 0.5, 8-connectivity; now the
-// merge takes 43 us instead of 22 and the link 23 instead of 17.
+// merge takes 41 us instead of 21 and the link 23 instead of 17.
 template <int TH, int NW, bool CONN8>
 __global__ void __launch_bounds__(NW * 64) k1_merge_stats(ImgView v, StatsView s) {
     static_assert(TH <= 64, "one mask word per tile row and 6-bit row offsets");
