@@ -61,7 +61,9 @@ __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, u
         uint64_t mine = 0ull;  // lane i: word i's mask
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
-            const uint64_t m = __ballot(l[i] == p[i] + 1u);
+            // (a lane outside the image holds 0, and its p + 1 wraps to 0 where
+            // H * W is close to 2^32)
+            const uint64_t m = __ballot(l[i] != 0u && l[i] == p[i] + 1u);
             if (lane == i) mine = m;
             cnt += (uint32_t)__popcll(m);
         }
