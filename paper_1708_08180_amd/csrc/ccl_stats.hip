@@ -31,7 +31,7 @@ namespace ccl {
 namespace {
 
 constexpr int kWordsPerBlock = 256;
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kEmpty = 0u;  // no component has label 0
 
 __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, uint32_t WW,
                                                  uint32_t words, uint64_t *mask, uint32_t *bsum) {
