@@ -424,7 +424,8 @@ int ccl_server_destroy(ccl_server *s);
  * ccl_autotune or ccl_tuning_load, misses use the built-in default:
  * tile_h 32 with 4 wavefronts below 2^22 pixels, tile_h 64 with 4 from
  * there up.  Equal-value labeling, which is not compiled for (32,4), takes
- * (32,8) below 2^22 pixels instead, and runs (64,4) as (64,8). */
+ * (32,8) below 2^22 pixels instead, and runs (64,4) as (64,8) where a launch
+ * of that many threads is possible. */
 
 /* Time every supported tile configuration on the given image (device
  * buffers as in ccl_label_2d; `labels` is overwritten), `reps` calls each,

@@ -276,8 +276,9 @@ int ccl_label_2d_equal(const uint8_t *img, int32_t H, int32_t W, int64_t pitch,
         }
         // 64-row tiles run 8 wavefronts here, one thread per eight columns of
         // a row (2160 x 3840 in six levels, 8-connectivity: 45.9 us a call,
-        // 49.0 with 4; 4096 x 4096 noise 106 and 118)
-        if (th == 64 && nw == 4) nw = 8;
+        // 49.0 with 4; 4096 x 4096 noise 106 and 118); 4 where a launch does
+        // not hold that many threads (images of very few rows or columns)
+        if (th == 64 && nw == 4 && grid_fits(ws_layout(H, W, th, true).tiles, 512u)) nw = 8;
     }
     hipStream_t s = (hipStream_t)stream;
     void *ws = nullptr;

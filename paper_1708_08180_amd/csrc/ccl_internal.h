@@ -75,6 +75,10 @@ inline WsLayout ws_layout(int H, int W, int th, bool equal = false) {
     return l;
 }
 
+// Whether a launch of `groups` workgroups of `threads` threads is one that HIP
+// accepts: fewer than 2^32 threads in all.
+inline bool grid_fits(uint64_t groups, unsigned threads) { return groups * threads <= 0xFFFFFFFFull; }
+
 // Shared by the entry points.
 int fail_hip(hipError_t e);
 // The library's workspace for (current device, stream), at least `need`
