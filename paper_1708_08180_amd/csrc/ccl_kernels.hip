@@ -608,8 +608,10 @@ static hipError_t launch_plain_t(const ImgView &v, hipStream_t stream, hipEvent_
         hipLaunchKernelGGL((k2_boundary<TH, CONN8, EQ>), dim3((tiles + 3) / 4), dim3(256), 0, stream,
                            v, tiles);
     if (ev) (void)hipEventRecord(ev[2], stream);
-    constexpr int NW3 = link_waves<TH>();
-    hipLaunchKernelGGL((k3_link<TH, NW3, EQ>), dim3(tiles), dim3(NW3 * 64), 0, stream, v);
+    with_link_waves<TH>(tiles, [&](auto nw3) {
+        constexpr int NW3 = decltype(nw3)::value;
+        hipLaunchKernelGGL((k3_link<TH, NW3, EQ>), dim3(tiles), dim3(NW3 * 64), 0, stream, v);
+    });
     if (ev) (void)hipEventRecord(ev[3], stream);
     return hipGetLastError();
 }

@@ -198,9 +198,8 @@ struct K3StatsLds {
     uint32_t ncomp;
 };
 
-template <int TH, bool CONN8>
-__global__ void __launch_bounds__(link_waves<TH>() * 64) k3_link_stats(ImgView v, StatsView s) {
-    constexpr int NW = link_waves<TH>();
+template <int TH, int NW, bool CONN8>
+__global__ void __launch_bounds__(NW * 64) k3_link_stats(ImgView v, StatsView s) {
     constexpr uint32_t NT = NW * 64;
     using LR = LinkRows<TH, NW, false>;
     constexpr int RPW = LR::RPW;
@@ -588,7 +587,10 @@ template <int TH, bool CONN8>
 hipError_t launch_stats_t(const ImgView &v, const StatsView &s, hipStream_t st) {
     const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
     const uint32_t ng = ((uint32_t)v.tilesX + kBandGroupTiles - 1u) / kBandGroupTiles;
-    hipLaunchKernelGGL((k3_link_stats<TH, CONN8>), dim3(tiles), dim3(link_waves<TH>() * 64), 0, st, v, s);
+    with_link_waves<TH>(tiles, [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        hipLaunchKernelGGL((k3_link_stats<TH, NW, CONN8>), dim3(tiles), dim3(NW * 64), 0, st, v, s);
+    });
     hipLaunchKernelGGL((st_band<TH, CONN8>), dim3((uint32_t)v.tilesY * ng), dim3(1024), 0, st, v, s);
     const uint32_t per = span_tiles<CONN8>((uint32_t)v.tilesX);
     hipLaunchKernelGGL((st_span<TH, CONN8>), dim3((uint32_t)v.tilesY * (((uint32_t)v.tilesX + per - 1u) / per)),

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "ccl_device.h"
+#include "ccl_internal.h"
 
 namespace ccl {
 
@@ -228,6 +229,18 @@ __device__ __forceinline__ void k3_tile(const ImgView &v, uint32_t t, const uint
 template <int TH>
 constexpr int link_waves() {
     return TH == 32 ? 4 : TH / 16;
+}
+
+// launch(waves per workgroup) for the link of `tiles` tiles: link_waves, or 16
+// rows per wave where a launch does not hold that many threads (a caller's
+// 32-row tiles of 1 or 2 wavefronts on images of very few rows or columns).
+template <int TH, class Launch>
+void with_link_waves(uint64_t tiles, Launch &&launch) {
+    constexpr int NW = link_waves<TH>();
+    if constexpr (NW > TH / 16) {
+        if (!grid_fits(tiles, NW * 64u)) return launch(std::integral_constant<int, TH / 16>{});
+    }
+    launch(std::integral_constant<int, NW>{});
 }
 
 }  // namespace ccl

@@ -26,3 +26,18 @@ def test_equal_value_thin_images(tmp_path):
     res = record([_equal(1, 64 * most), _equal(64 * most, 1, 4), _equal(1, 64 * (most // 2)), _equal(2160, 3840)], tmp_path)
     _accepted(res)
     assert [ls[0][3] for _, ls in res] == [256, 256, 512, 512]
+
+
+@pytest.mark.parametrize("conn", [4, 8])
+def test_link_of_thin_images(tmp_path, conn):
+    # 32-row tiles of one and two wavefronts: the local merge needs 64 and 128
+    # threads a tile, and the link no more than 128
+    most = (2 ** 32 - 1) // 128
+    calls = [_plain(1, 64 * most - 5, conn, ("cfg", 32, nw)) for nw in (1, 2)]
+    calls += [_plain(32 * most // 2, 1, conn, ("cfg", 32, 2)), _equal(1, 64 * most - 5, conn, ("cfg", 32, 2))]
+    calls += [("ccl_label_2d_stats", [IMG, 1, 64 * most - 5, 64 * most - 5, conn, LABELS, OUT, 1, COUNT, ("cfg", 32, nw), None])
+              for nw in (1, 2)]
+    _accepted(record(calls, tmp_path))
+    # elsewhere four wavefronts
+    for _, ls in record([_plain(480, 640, conn), _plain(480, 640, conn, ("cfg", 32, 1))], tmp_path):
+        assert ls[-1][3] == 256
