@@ -601,6 +601,9 @@ __global__ void __launch_bounds__(NW * 64) k3_batch(BatchArgs a) {
 template <int TH, int NW, bool CONN8, bool EQ>
 static hipError_t launch_plain_t(const ImgView &v, hipStream_t stream, hipEvent_t *ev) {
     const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
+    // a grid that HIP would refuse: the later phases must not run on a
+    // workspace that the local merge has not written
+    if (!grid_fits(tiles, (NW > TH / 16 ? NW : TH / 16) * 64u)) return hipErrorInvalidConfiguration;
     if (ev) (void)hipEventRecord(ev[0], stream);
     hipLaunchKernelGGL((k1_local_merge<TH, NW, CONN8, EQ>), dim3(tiles), dim3(NW * 64), 0, stream, v);
     if (ev) (void)hipEventRecord(ev[1], stream);

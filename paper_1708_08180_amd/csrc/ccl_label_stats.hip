@@ -598,6 +598,15 @@ hipError_t launch_stats_t(const ImgView &v, const StatsView &s, hipStream_t st) 
     return hipGetLastError();
 }
 
+// Whether every launch of a call is one that HIP accepts (its later kernels
+// must not run on what an earlier, refused one has not written).
+template <bool CONN8>
+bool stats_grids_fit(const ImgView &v, int th, int nw) {
+    const uint64_t TX = (uint64_t)v.tilesX, TY = (uint64_t)v.tilesY, per = span_tiles<CONN8>((uint32_t)TX);
+    return grid_fits(TX * TY, (unsigned)max(nw, th / 16) * 64u) &&
+           grid_fits(TY * ((TX + kBandGroupTiles - 1u) / kBandGroupTiles), 1024u) && grid_fits(TY * ((TX + per - 1u) / per), 1024u);
+}
+
 hipError_t launch_merge_stats(const ImgView &v, const StatsView &s, int th, int nw, int conn, hipStream_t st) {
     const uint32_t tiles = (uint32_t)v.tilesX * (uint32_t)v.tilesY;
 #define CCL_CASE(T, N)                                                                              \
@@ -672,6 +681,8 @@ extern "C" int ccl_label_2d_stats(const uint8_t *img, int32_t H, int32_t W, int6
     s.out = out;
     s.n_out = n_out;
     s.cap = capacity > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)capacity;
+    if (!(connectivity == 8 ? stats_grids_fit<true>(v, th, nw) : stats_grids_fit<false>(v, th, nw)))
+        return fail_hip(hipErrorInvalidConfiguration);
     hipError_t e = launch_merge_stats(v, s, th, nw, connectivity, st);
     if (e == hipSuccess) e = launch_boundary(v, th, connectivity, st);
     if (e == hipSuccess) e = launch_stats(v, s, th, connectivity, st);

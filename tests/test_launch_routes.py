@@ -41,3 +41,15 @@ def test_link_of_thin_images(tmp_path, conn):
     # elsewhere four wavefronts
     for _, ls in record([_plain(480, 640, conn), _plain(480, 640, conn, ("cfg", 32, 1))], tmp_path):
         assert ls[-1][3] == 256
+
+
+def test_nothing_runs_when_a_launch_is_refused(tmp_path):
+    # sixteen wavefronts a tile do not fit; the boundary analysis and the link
+    # would read a workspace that no local merge has written
+    n = 600000000
+    calls = [_plain(1, n, 8, ("cfg", 64, 16)), _plain(1, n, 4, ("cfg", 32, 16)), _plain(n, 1, 8, ("cfg", 128, 16)),
+             _equal(1, 1200000000), ("ccl_label_2d_timed", [IMG, 1, n, n, 8, LABELS, ("cfg", 64, 16), None, 0]),
+             ("ccl_label_2d_stats", [IMG, 1, n, n, 8, LABELS, OUT, 1, COUNT, ("cfg", 64, 16), None]),
+             ("ccl_label_2d_stats", [IMG, n, 1, 1, 4, LABELS, OUT, 1, COUNT, ("cfg", 16, 1), None])]
+    for rc, launches in record(calls, tmp_path):
+        assert rc == 4 and not launches
