@@ -412,7 +412,15 @@ constexpr int kSmallLines = 256;
 template <bool CONN8>
 struct SmallLds {
     static constexpr int NODES = kSmallLines * (CONN8 ? 32 : 64);
-    static constexpr int JOINS = 4096;
+    // Room for every join: a line's intervals touch at most 33 of the line
+    // above (its 64 columns and, under 8-connectivity, one beside each end),
+    // and along a line the touching pairs are one fewer than the intervals on
+    // both sides; each lower interval's first pair is a hook, so a line lists
+    // at most 32 joins, and one more with the word before.  (With 4096 entries the
+    // joins that did not fit were made at once, among the uncompressed hooks:
+    // columns staggered every other row, 8-connectivity, 128 x 192, 58.5 us a
+    // call; so 16.1.)
+    static constexpr int JOINS = 33 * kSmallLines;
     alignas(16) LineForest<kSmallLines, NODES, JOINS, NODES> f;
     uint64_t m[2][kSmallLines];  // top / bottom row masks of every line
     uint32_t part[4], nodes;
