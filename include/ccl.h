@@ -99,10 +99,11 @@ int ccl_version(void);
  * wait.  ccl_shutdown releases it.  Calls on the same stream, from any
  * thread, are ordered by the stream; calls on different streams use
  * different workspaces.  Callers that must not allocate at all pass their
- * own workspace to ccl_label_2d_ex.  Images of at most 256 lines (two rows of
- * 64 columns: ceil(H/2) * ceil(W/64)) for which neither the caller nor the
+ * own workspace to ccl_label_2d_ex.  Images of few lines (two rows of 64
+ * columns: ceil(H/2) * ceil(W/64)) for which neither the caller nor the
  * tuning table names a tile configuration are labeled in one launch that
- * needs no workspace.
+ * needs no workspace: at most 120 lines under 4-connectivity; 128 under
+ * 8-connectivity, 192 from 48 rows up.
  * Returns CCL_OK or an error; on error nothing has been enqueued (except
  * CCL_ERR_HIP from a failed launch).
  */

@@ -206,7 +206,7 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
     }
     // small images that neither the caller nor the tuning table chose a
     // configuration for are labeled in one launch, without a workspace
-    if (builtin && small_image(H, W)) {
+    if (builtin && small_image(H, W, connectivity)) {
         const hipError_t e = launch_small(make_view(img, H, W, pitch, labels, nullptr, th), connectivity, s);
         return e == hipSuccess ? CCL_OK : fail_hip(e);
     }

@@ -37,7 +37,7 @@ hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t 
 
 // Images that label_small takes whole (binary labeling; one launch, no
 // workspace), and that launch.
-bool small_image(int H, int W);
+bool small_image(int H, int W, int conn);
 hipError_t launch_small(const ImgView &v, int conn, hipStream_t s);
 
 // The boundary analysis of binary labeling for one image on `s`, without the

@@ -403,15 +403,16 @@ __global__ void __launch_bounds__(NW * 64) k3_link(ImgView v) {
 // the whole image, whose lines are the 64-column words of its bands in raster
 // order, with joins between neighbouring words of a band; the labels are
 // written from LDS.  Such a call is bound by launches and by the latency of a
-// phase, not by work: 120 x 160 takes 16.6 us in three launches and 9.5 so.
-// The line lies where one compute unit's 16 wavefronts still keep up: at 192
-// lines of noise 14.5 us against 19.4, and the LDS of 256 lines of 64
-// intervals (4-connectivity) is 129 KB.
-constexpr int kSmallLines = 256;
+// phase, not by work: 64 x 64 of noise takes 12 us in three launches and 6 so,
+// 120 x 160 19 and 15 where the columns are staggered, 13 and 10 in noise.
+// small_image() holds where the line lies.
+template <bool CONN8>
+constexpr int kSmallLines = CONN8 ? 192 : 128;  // room for, a multiple of 64
 
 template <bool CONN8>
 struct SmallLds {
-    static constexpr int NODES = kSmallLines * (CONN8 ? 32 : 64);
+    static constexpr int LINES = kSmallLines<CONN8>;
+    static constexpr int NODES = LINES * (CONN8 ? 32 : 64);
     // Room for every join: a line's intervals touch at most 33 of the line
     // above (its 64 columns and, under 8-connectivity, one beside each end),
     // and along a line the touching pairs are one fewer than the intervals on
@@ -420,10 +421,10 @@ struct SmallLds {
     // joins that did not fit were made at once, among the uncompressed hooks:
     // columns staggered every other row, 8-connectivity, 128 x 192, 58.5 us a
     // call; so 16.1.)
-    static constexpr int JOINS = 33 * kSmallLines;
-    alignas(16) LineForest<kSmallLines, NODES, JOINS, NODES> f;
-    uint64_t m[2][kSmallLines];  // top / bottom row masks of every line
-    uint32_t part[4], nodes;
+    static constexpr int JOINS = 33 * LINES;
+    alignas(16) LineForest<LINES, NODES, JOINS, NODES> f;
+    uint64_t m[2][LINES];  // top / bottom row masks of every line
+    uint32_t part[LINES / 64], nodes;
 };
 
 template <bool CONN8>
@@ -451,7 +452,7 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
     __syncthreads();
     // every line's intervals, and their numbering (a line per thread)
     uint32_t ex = 0u;
-    if (wave < kSmallLines / 64) {
+    if (wave < SmallLds<CONN8>::LINES / 64) {
         const bool in = tid < lines;
         const uint64_t t0 = in ? sh.m[0][tid] : 0ull, b0 = in ? sh.m[1][tid] : 0ull;
         const uint64_t S = band_starts<CONN8>(t0, b0);
@@ -461,10 +462,10 @@ __global__ void __launch_bounds__(1024) label_small(ImgView v) {
         if (lane == 0) sh.part[wave] = total;
     }
     __syncthreads();
-    if (wave < kSmallLines / 64) {
+    if (wave < SmallLds<CONN8>::LINES / 64) {
         uint32_t before = 0u, all = 0u;
 #pragma unroll
-        for (int j = 0; j < kSmallLines / 64; ++j) {
+        for (int j = 0; j < SmallLds<CONN8>::LINES / 64; ++j) {
             before += j < wave ? sh.part[j] : 0u;
             all += sh.part[j];
         }
@@ -692,8 +693,20 @@ hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t 
     return hipErrorInvalidValue;
 }
 
-bool small_image(int H, int W) {
-    return ((int64_t)H + 1) / 2 * (((int64_t)W + kTileW - 1) / kTileW) <= kSmallLines;
+// One launch where no image of the size measured slower in it than in three, be
+// it noise, stripes, a checkerboard or staggered columns (us a call; the three
+// launches with 4 wavefronts in the merge, which ran all sizes before):
+//   4-connectivity, a checkerboard (most nodes): 120 lines 8.8 against 9.4,
+//     128 lines of 4 rows 9.3 and 9.1, 128 x 256 (256 lines) 16.2 and 10.5;
+//   8-connectivity, at most one row of 32-row tiles (columns): 128 lines of 32
+//     rows 8.8 and 9.8, 160 lines 10.2 and 9.8, 8 x 4096 14.1 and 9.2;
+//   8-connectivity, more rows, where the three launches join tiles below each
+//     other (staggered columns): 192 lines of 48 rows 15.8 and 17.3, 160 x 160
+//     (240 lines) 18.9 both, 512 x 64 19.9 and 18.6.
+bool small_image(int H, int W, int conn) {
+    const int64_t lines = ((int64_t)H + 1) / 2 * (((int64_t)W + kTileW - 1) / kTileW);
+    if (conn == 4) return lines <= 120;
+    return lines <= (H >= 48 ? 192 : 128);
 }
 
 hipError_t launch_small(const ImgView &v, int conn, hipStream_t s) {

@@ -1,14 +1,20 @@
 """Small images with as many joins as their lines can list: columns staggered
-every other row touch two intervals of the line above each."""
+every other row touch two intervals of the line above each; and the sizes where
+one launch ends and three begin."""
 import numpy as np
 import pytest
 
 import oracle
+from paper_1708_08180_amd import workloads as wl
 from tests.gpu_util import say, to_dev
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(120, 160), (128, 192), (192, 128), (129, 130), (128, 256), (512, 64), (127, 250)]
+# the last three rows: the first and last sizes of one launch and of three
+SHAPES = [(120, 160), (128, 192), (192, 128), (129, 130), (128, 256), (512, 64), (127, 250),
+          (240, 64), (241, 64), (2, 7680), (2, 7681), (47, 320),
+          (256, 64), (257, 64), (32, 512), (32, 513), (2, 8192), (2, 8193),
+          (48, 512), (48, 513), (384, 64), (385, 64)]
 
 
 def _staggered(H, W, step=2):
@@ -22,11 +28,11 @@ def test_many_joins(shape, conn):
     import torch
     from paper_1708_08180_amd import binding
 
-    for step in (1, 2, 3):
-        img = _staggered(*shape, step)
+    images = [_staggered(*shape, step) for step in (1, 2, 3)] + [wl.bernoulli(*shape, p, 4400) for p in (0.4, 0.6)]
+    for k, img in enumerate(images):
         out = binding.label(to_dev(img), conn)
         torch.cuda.synchronize()
-        assert np.array_equal(out.cpu().numpy().view(np.uint32), oracle.label(img, conn)), step
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), oracle.label(img, conn)), k
 
 
 @pytest.mark.parametrize("shape", [(120, 160), (128, 192)])
