@@ -100,9 +100,9 @@ int ccl_version(void);
  * thread, are ordered by the stream; calls on different streams use
  * different workspaces.  Callers that must not allocate at all pass their
  * own workspace to ccl_label_2d_ex.  Images of few lines (two rows of 64
- * columns: ceil(H/2) * ceil(W/64)) for which neither the caller nor the
- * tuning table names a tile configuration are labeled in one launch that
- * needs no workspace: at most 120 lines under 4-connectivity; 128 under
+ * columns: ceil(H/2) * ceil(W/64)) for which the caller names no tile
+ * configuration are labeled in one launch that needs no workspace, whatever
+ * the tuning table holds: at most 120 lines under 4-connectivity; 128 under
  * 8-connectivity, 192 from 48 rows up.
  * Returns CCL_OK or an error; on error nothing has been enqueued (except
  * CCL_ERR_HIP from a failed launch).
@@ -432,11 +432,16 @@ int ccl_server_destroy(ccl_server *s);
  * buffers as in ccl_label_2d; `labels` is overwritten), `reps` calls each,
  * and record the fastest for the image's size class and connectivity.
  * Writes the winner to *best and its mean milliseconds per call to
- * *best_ms (either may be NULL).  Blocks. */
+ * *best_ms (either may be NULL).  Blocks.  Images that ccl_label_2d labels in
+ * one launch keep that launch; their class's entry serves the other entry
+ * points and the class's larger images. */
 int ccl_autotune(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int32_t connectivity,
                  uint32_t *labels, int32_t reps, void *stream, ccl_config *best, float *best_ms);
 
-/* Look up the configuration ccl_label_2d would use for H x W. */
+/* Look up the configuration for H x W: the table's, else the built-in default.
+ * It is that of the phases; images that ccl_label_2d labels in one launch do
+ * not use it there, and where it is the default (32,4) the local merge of
+ * ccl_label_2d runs 8 wavefronts on those tiles. */
 int ccl_tuning_get(int32_t H, int32_t W, int32_t connectivity, ccl_config *out);
 
 /* Save / load the tuning table as JSON lines

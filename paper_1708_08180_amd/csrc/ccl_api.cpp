@@ -204,9 +204,12 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
         if (workspace_bytes < need) return CCL_ERR_WORKSPACE;
         if (((uintptr_t)ws & 255u) != 0) return CCL_ERR_INVALID_ARG;
     }
-    // small images that neither the caller nor the tuning table chose a
-    // configuration for are labeled in one launch, without a workspace
-    if (builtin && small_image(H, W, connectivity)) {
+    // small images that the caller chose no configuration for are labeled in
+    // one launch, without a workspace.  The tuning table holds configurations of
+    // the three launches, the fastest of which is seldom as fast (120 x 160
+    // noise 16 us a call, 10 in one launch)
+    const bool chosen = cfg && (cfg->tile_h != 0 || cfg->waves != 0);
+    if (!chosen && small_image(H, W, connectivity)) {
         const hipError_t e = launch_small(make_view(img, H, W, pitch, labels, nullptr, th), connectivity, s);
         return e == hipSuccess ? CCL_OK : fail_hip(e);
     }

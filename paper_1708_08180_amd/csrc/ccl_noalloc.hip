@@ -58,7 +58,7 @@ extern "C" int ccl_label_2d_noalloc(const uint8_t *img, int32_t H, int32_t W, in
     // rejected before any HIP call: the image needs more workspace than the
     // fixed array holds
     if (ws_layout(H, W, th).total > (size_t)CCL_NOALLOC_SCRATCH_BYTES) return CCL_ERR_WORKSPACE;
-    if (builtin && small_image(H, W, connectivity)) {  // one launch that needs no workspace
+    if (small_image(H, W, connectivity)) {  // one launch that needs no workspace
         const hipError_t e = launch_small(make_view(img, H, W, pitch, labels, nullptr, th), connectivity, (hipStream_t)stream);
         return e == hipSuccess ? CCL_OK : fail_hip(e);
     }

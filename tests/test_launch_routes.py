@@ -66,3 +66,18 @@ def test_sizes_of_one_launch(tmp_path, fn):
              for s in one + three]
     for size, (rc, ls) in zip(one + three, record(calls, tmp_path)):
         assert rc == 0 and len(ls) == (1 if size in one else 3 if size[0] > 32 or size[1] > 64 else 2), (size, ls)
+
+
+def test_tuning_leaves_small_images_in_one_launch(tmp_path):
+    table = tmp_path / "tuning.jsonl"
+    table.write_text('{"class": 14, "conn": 8, "tile_h": 64, "waves": 2, "ms": 0.01}\n')
+    small, noalloc = _plain(120, 160), ("ccl_label_2d_noalloc", [IMG, 120, 160, 160, 8, LABELS, None])
+    thin = _plain(20000, 1)  # of the same class, with too many lines
+    calls = [small, ("ccl_tuning_load", [str(table)]), small, noalloc, thin, _plain(120, 160, 8, ("cfg", 64, 2)),
+             ("ccl_autotune", [IMG, 120, 160, 160, 8, LABELS, 1, None, None, None]), small, thin]
+    res = record(calls, tmp_path)
+    assert all(rc == 0 for rc, _ in res)
+    assert [len(res[i][1]) for i in (0, 2, 3, 7)] == [1, 1, 1, 1]
+    assert res[4][1][0][0] == "k1_local_merge<64, 2, true, false>"
+    assert len(res[5][1]) == 3
+    assert len(res[8][1]) == 3 and res[8][1][0][0] != "k1_local_merge<32, 8, true, false>"
