@@ -159,7 +159,9 @@ int ccl_label_2d_noalloc(const uint8_t *img, int32_t H, int32_t W, int64_t pitch
  * done and writes the elapsed milliseconds of phase 1 (local merge), phase 2
  * (boundary analysis) and phase 3 (link) to phase_ms[0..2] (host array of 3
  * floats).  Same labels and errors as ccl_label_2d_ex (library workspace).
- * Meant for measurement; the events add a few microseconds per call.
+ * Meant for measurement; the events add a few microseconds per call.  The
+ * phases run with the grids of ccl_label_2d_ex; images that it labels in one
+ * launch, which has no phases, are labeled in three here.
  */
 int ccl_label_2d_timed(const uint8_t *img, int32_t H, int32_t W, int64_t pitch,
                        int32_t connectivity, uint32_t *labels, const ccl_config *cfg,

@@ -236,7 +236,8 @@ int ccl_label_2d_timed(const uint8_t *img, int32_t H, int32_t W, int64_t pitch,
     if (rc != CCL_OK) return rc;
     if (connectivity != 4 && connectivity != 8) return CCL_ERR_UNSUPPORTED;
     int th = 0, nw = 0;
-    rc = resolve_config(H, W, connectivity, cfg, &th, &nw);
+    bool builtin = false;
+    rc = resolve_config(H, W, connectivity, cfg, &th, &nw, &builtin);
     if (rc != CCL_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
     void *ws = nullptr;
@@ -248,7 +249,7 @@ int ccl_label_2d_timed(const uint8_t *img, int32_t H, int32_t W, int64_t pitch,
     for (int i = 0; i < 4 && e == hipSuccess; ++i) e = hipEventCreate(&ev[i]);
     if (e == hipSuccess) {
         const ImgView v = make_view(img, H, W, pitch, labels, ws, th);
-        e = launch_plain(v, th, nw, connectivity, s, ev);
+        e = launch_plain(v, th, builtin ? merge_waves(th, nw) : nw, connectivity, s, ev);
     }
     held.unlock();
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);

@@ -81,3 +81,14 @@ def test_tuning_leaves_small_images_in_one_launch(tmp_path):
     assert res[4][1][0][0] == "k1_local_merge<64, 2, true, false>"
     assert len(res[5][1]) == 3
     assert len(res[8][1]) == 3 and res[8][1][0][0] != "k1_local_merge<32, 8, true, false>"
+
+
+def test_timed_call_launches_what_the_plain_call_does(tmp_path):
+    calls = []
+    for H, W, conn in ((480, 640, 8), (480, 640, 4), (1080, 1920, 8), (2160, 3840, 4)):
+        for cfg in (None, ("cfg", 32, 4), ("cfg", 64, 8)):
+            calls += [_plain(H, W, conn, cfg), ("ccl_label_2d_timed", [IMG, H, W, W, conn, LABELS, cfg, None, 0])]
+    res = record(calls, tmp_path)
+    _accepted(res)
+    for k in range(0, len(res), 2):
+        assert res[k] == res[k + 1], calls[k]
