@@ -172,8 +172,11 @@ def _stream_handle(stream):
     torch = _torch()
     if stream is None:
         # the current device's current stream, without building a Stream
-        # object for it (0.1 against 3 us a call)
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        # object for it where torch can say (0.1 against 3 us a call)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return ctypes.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
 
 
