@@ -54,7 +54,6 @@ template <int TH, int NW, bool CONN8>
 __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds<TH> &sh) {
     static_assert(TH <= 64, "one lane per row");
     constexpr int SPR = slots_per_row<true>();
-    constexpr int RPW = TH / NW;
     constexpr int NT = NW * 64;
     constexpr int CH = TH * 4;                  // 16-byte chunks per tile
     constexpr int LPT = (CH + NT - 1) / NT;     // chunks per thread

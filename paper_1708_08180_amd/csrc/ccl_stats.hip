@@ -75,8 +75,12 @@ __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, u
 }
 
 // Blocks whose counts every block of st_bases adds up by itself.  The sums
-// read nb * nb / 2 counts from the L2, 8 MB at 2048 blocks (128 Mpixels);
-// a scan in a launch of its own takes 4 to 5 us whatever the size.
+// read nb * nb / 2 counts from the L2, 8 MB at 2048 blocks (32 Mi pixels where
+// W is a multiple of 64); a scan is a launch of its own.  Counting background
+// only, with the sums and with the scan: 1080 x 1920 12.7 and 15.6 us, 4096 x
+// 4096 (1024 blocks) 30.4 and 32.7, 4096 x 8192 (2048) 53.9 and 55.9, 8192 x 8192
+// (4096) 97.8 and 100.0, 12288 x 12288 (9216) 249.9 and 246.5; between 2048 and
+// 8192 blocks there is 2 % in it.
 constexpr uint32_t kSelfScanBlocks = 2048u;
 
 __global__ void __launch_bounds__(1024) st_scan(uint32_t *bsum, uint32_t nb) {
@@ -199,6 +203,11 @@ constexpr int kAccSlots = 1024;
 // the blocks of 64 columns.  With half the workgroups 2160 x 3840 smoothed
 // takes 42 us instead of 50, but dense small components lose 4 %.
 constexpr uint32_t kAccMaxBlocks = 8u, kAccGroups = 512u;
+// the table's 32-bit coordinate sums hold a workgroup whose pixels all have one
+// label
+static_assert((uint64_t)kAccCols * kAccRows * kAccMaxBlocks * (kAccRows * kAccMaxBlocks - 1u) <= 0xFFFFFFFFull &&
+                  (uint64_t)kAccCols * kAccRows * kAccMaxBlocks * (kAccCols - 1) <= 0xFFFFFFFFull,
+              "coordinate sums relative to the workgroup's first pixel fit 32 bits");
 // Labels gathered over the strip at most (with 256-row blocks 1, 2, 4 and 8
 // measured 28.1, 27.6, 29.0 and 30.3 us), and the pixels a gathered label must have had for another
 // one to be tried: a strip of small components is cheaper run by run.
