@@ -39,7 +39,12 @@ namespace ccl {
 // one after the other took 39.5.
 template <int TH>
 struct K1EqLds {
-    static constexpr int JOINS = 32 * TH;
+    // Room for every join: a run of m pixels touches at most (m + 3) / 2 runs of
+    // its value in the row above, the first of which is its hook, so a row of 64
+    // lists at most 64.  (Joins that did not fit 32 per row were made at once,
+    // among the uncompressed hooks: local merge of a 4096 x 4096 checkerboard,
+    // 8-connectivity, 343 us; so 94.)
+    static constexpr int JOINS = 64 * TH;
     alignas(16) LineForest<TH, TH * 64, JOINS, 0> f;
     uint64_t S[TH];         // per row: run starts
     uint64_t flg[TH];       // per row: local roots of edge-touching components
