@@ -151,9 +151,13 @@ __device__ __forceinline__ void k1_tile_eq(const ImgView &v, uint32_t t, K1EqLds
         if (i >= 8) forest_hooks<CONN8>(F, i >> 3, i & 7);
     __syncthreads();
     const uint32_t nodes = sh.nodes, joins = min(F.joins, (uint32_t)K1EqLds<TH>::JOINS);
+    // (Also without joins: chains are as deep as the tile where runs go straight
+    // down, and the walks of the record phase, eight columns apart, meet on
+    // eight of the LDS banks.  Local merge of 4096 x 4096 columns, 4-connectivity: 96 us
+    // without it, 56 so; a checkerboard, which hooks nothing, 30 and 33.)
+    compress_nodes<NT>(par, nodes, [](uint32_t) {});
+    __syncthreads();
     if (joins) {  // workgroup-uniform
-        compress_nodes<NT>(par, nodes, [](uint32_t) {});
-        __syncthreads();
         for (uint32_t i = (uint32_t)tid; i < joins; i += NT) {
             const uint32_t e = F.join[i];
             lds_link(par, parent_of(par, e & 0xFFFFu), parent_of(par, e >> 16));

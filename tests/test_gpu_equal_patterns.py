@@ -67,3 +67,8 @@ def _against_noise(name, conn):
 def test_joins_that_fit_the_list():
     # 3.6 times the time of noise when the list was too short for them
     assert _against_noise("checkerboard", 8) < 2.0
+
+
+def test_deep_chains():
+    # 1.6 times the time of noise when every run walked up the whole tile
+    assert _against_noise("columns", 4) < 1.4
