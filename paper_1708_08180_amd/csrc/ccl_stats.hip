@@ -193,7 +193,9 @@ __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t W
 // components, but up to 7 % more where components are many and small
 // (4-connectivity, p = 0.3), with half as many workgroups to share them.
 constexpr int kAccWaves = 16, kAccStripRows = 16;
-constexpr int kAccCols = 2 * kTileW, kAccRows = kAccWaves / 2 * kAccStripRows;
+constexpr int kAccCols = 2 * kTileW;
+constexpr int acc_rows(int waves) { return waves / 2 * kAccStripRows; }
+constexpr int kAccRows = acc_rows(kAccWaves);
 constexpr int kAccSlots = 1024;
 // A workgroup takes up to this many blocks below each other, as many as leave
 // two workgroups per compute unit (kAccGroups), and flushes when its table is
@@ -208,6 +210,24 @@ constexpr uint32_t kAccMaxBlocks = 8u, kAccGroups = 512u;
 static_assert((uint64_t)kAccCols * kAccRows * kAccMaxBlocks * (kAccRows * kAccMaxBlocks - 1u) <= 0xFFFFFFFFull &&
                   (uint64_t)kAccCols * kAccRows * kAccMaxBlocks * (kAccCols - 1) <= 0xFFFFFFFFull,
               "coordinate sums relative to the workgroup's first pixel fit 32 bits");
+// Wavefronts per block: 16, but 4 (blocks of 32 rows) or 8 (64 rows) on images
+// of few blocks.  There a block of 128 x 128 leaves the chip idle while one
+// workgroup adds the runs of 16384 pixels, whose components may also be more
+// than its table has slots for; on larger images the small blocks' flushes of
+// one large component follow each other.  Worst over noise of p = 0.1 .. 0.9,
+// smoothed fields and blobs, as a share of the speed of 64 x 256 blocks:
+//   128 x 128    16 waves 0.60, 8 0.97, 4 1.08
+//   480 x 640    (75 blocks of 32 rows) 0.83, 1.15, 1.00
+//   640 x 800    (140; 70 of 64 rows) 0.94, 1.06, 0.84
+//   720 x 1280   (240; 120) 1.00, 1.00, 0.74
+//   1080 x 1920  (510; 255) 1.02, 0.85, 0.54
+//   60 x 8192    (128; 64) 0.78, 0.76, 1.00
+inline int acc_waves(uint32_t H, uint32_t W) {
+    const uint64_t cols = ((uint64_t)W + kAccCols - 1u) / kAccCols;
+    auto blocks = [&](int waves) { return cols * (((uint64_t)H + acc_rows(waves) - 1u) / acc_rows(waves)); };
+    if (blocks(4) <= (H <= 64u ? 128u : 96u)) return 4;
+    return blocks(8) <= 128u ? 8 : kAccWaves;
+}
 // Labels gathered over the strip at most (with 256-row blocks 1, 2, 4 and 8
 // measured 28.1, 27.6, 29.0 and 30.3 us), and the pixels a gathered label must have had for another
 // one to be tried: a strip of small components is cheaper run by run.
@@ -215,8 +235,8 @@ constexpr int kAccGather = 2;
 constexpr uint32_t kAccGatherPixels = 24u;
 
 // SEVERAL: more than one block per workgroup.
-template <bool SEVERAL>
-__global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L, uint32_t H, uint32_t W,
+template <int WAVES, bool SEVERAL>
+__global__ void __launch_bounds__(WAVES * 64, 8) st_accum(const uint32_t *L, uint32_t H, uint32_t W,
                                                           uint32_t WW, const uint64_t *mask,
                                                           const uint32_t *base, ccl_component *out,
                                                           uint32_t cap, uint32_t blocks) {
@@ -226,7 +246,8 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
     __shared__ uint32_t key[kAccSlots], area[kAccSlots], xmn[kAccSlots], ymn[kAccSlots],
         xmx[kAccSlots], ymx[kAccSlots], sx[kAccSlots], sy[kAccSlots];
     __shared__ uint32_t used;
-    constexpr int NT = kAccWaves * 64;
+    constexpr int NT = WAVES * 64;
+    constexpr uint32_t kRows = acc_rows(WAVES);
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto clear = [&] {
@@ -241,7 +262,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
     };
     clear();
     __syncthreads();
-    const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * (uint32_t)kAccRows * per;
+    const uint32_t bx = blockIdx.x * (uint32_t)kAccCols, by = blockIdx.y * kRows * per;
     const uint32_t xr = (uint32_t)(wave & 1) * kTileW;  // the wavefront's first column and row in the block
     const uint32_t n = H * W;
     const uint32_t x = bx + xr + (uint32_t)lane;
@@ -276,8 +297,8 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
         to_record(l, len, xa, xb, ya, yb, sxv, syv);
     };
 #pragma unroll 1
-    for (uint32_t j = 0; j < per && by + j * kAccRows < H; ++j) {  // workgroup-uniform
-        const uint32_t yw = j * kAccRows + (uint32_t)(wave >> 1) * kAccStripRows;
+    for (uint32_t j = 0; j < per && by + j * kRows < H; ++j) {  // workgroup-uniform
+        const uint32_t yw = j * kRows + (uint32_t)(wave >> 1) * kAccStripRows;
         // all the strip's rows are loaded first, so the loads overlap
         uint32_t lv[kAccStripRows];
 #pragma unroll
@@ -333,7 +354,7 @@ __global__ void __launch_bounds__(kAccWaves * 64, 8) st_accum(const uint32_t *L,
             add_lds(l, len, xa, xb, y, y, len * (xa + xb) / 2u, len * y);
         }
         __syncthreads();
-        const bool last = j + 1u == per || by + (j + 1u) * kAccRows >= H;
+        const bool last = j + 1u == per || by + (j + 1u) * kRows >= H;
         if (SEVERAL) {
             const bool full = used > (uint32_t)kAccSlots / 2u;
             __syncthreads();  // every wavefront has read it before the next block counts on
@@ -396,12 +417,16 @@ extern "C" int ccl_component_stats(const uint32_t *labels, int32_t H, int32_t W,
     const uint32_t cols = ((uint32_t)W + kAccCols - 1u) / kAccCols, rows = ((uint32_t)H + kAccRows - 1u) / kAccRows;
     const uint64_t per = min((uint64_t)kAccMaxBlocks, max((uint64_t)1, (uint64_t)cols * rows / kAccGroups));
     const dim3 grid(cols, (rows + (uint32_t)per - 1u) / (uint32_t)per);
-    if (per > 1u)
-        hipLaunchKernelGGL(st_accum<true>, grid, dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base,
-                           out, cap, (uint32_t)per);
-    else
-        hipLaunchKernelGGL(st_accum<false>, grid, dim3(kAccWaves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base,
-                           out, cap, 1u);
+    auto accumulate = [&](auto kernel, dim3 g, int waves) {
+        hipLaunchKernelGGL(kernel, g, dim3(waves * 64), 0, s, labels, (uint32_t)H, (uint32_t)W, WW, mask, base, out, cap,
+                           (uint32_t)per);
+    };
+    const int waves = acc_waves((uint32_t)H, (uint32_t)W);
+    const dim3 small(cols, ((uint32_t)H + acc_rows(waves) - 1u) / acc_rows(waves));
+    if (waves == 4) accumulate(st_accum<4, false>, small, 4);
+    else if (waves == 8) accumulate(st_accum<8, false>, small, 8);
+    else if (per > 1u) accumulate(st_accum<kAccWaves, true>, grid, kAccWaves);
+    else accumulate(st_accum<kAccWaves, false>, grid, kAccWaves);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
