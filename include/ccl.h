@@ -443,7 +443,7 @@ int ccl_autotune(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int32_
 /* Look up the configuration for H x W: the table's, else the built-in default.
  * It is that of the phases; images that ccl_label_2d labels in one launch do
  * not use it there, and where it is the default (32,4) the local merge of
- * ccl_label_2d runs 8 wavefronts on those tiles. */
+ * ccl_label_2d runs 8 wavefronts on up to 512 tiles under 4-connectivity. */
 int ccl_tuning_get(int32_t H, int32_t W, int32_t connectivity, ccl_config *out);
 
 /* Save / load the tuning table as JSON lines

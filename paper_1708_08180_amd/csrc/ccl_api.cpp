@@ -218,7 +218,7 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
         if (rc != CCL_OK) return rc;
     }
     const ImgView v = make_view(img, H, W, pitch, labels, ws, th);
-    const hipError_t e = launch_plain(v, th, builtin ? merge_waves(th, nw) : nw, connectivity, s);
+    const hipError_t e = launch_plain(v, th, builtin ? merge_waves(v, th, nw, connectivity) : nw, connectivity, s);
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
 }
@@ -249,7 +249,7 @@ int ccl_label_2d_timed(const uint8_t *img, int32_t H, int32_t W, int64_t pitch,
     for (int i = 0; i < 4 && e == hipSuccess; ++i) e = hipEventCreate(&ev[i]);
     if (e == hipSuccess) {
         const ImgView v = make_view(img, H, W, pitch, labels, ws, th);
-        e = launch_plain(v, th, builtin ? merge_waves(th, nw) : nw, connectivity, s, ev);
+        e = launch_plain(v, th, builtin ? merge_waves(v, th, nw, connectivity) : nw, connectivity, s, ev);
     }
     held.unlock();
     if (e == hipSuccess) e = hipEventSynchronize(ev[3]);

@@ -99,13 +99,18 @@ bool byte_ranges_overlap(const void *a, unsigned __int128 na, const void *b, uns
 // built-in one.  *builtin (may be null): neither chose one.
 int resolve_config(int H, int W, int conn, const ccl_config *cfg, int *th, int *nw, bool *builtin = nullptr);
 void default_config(int H, int W, int conn, int *th, int *nw, bool *builtin = nullptr);
-// Wavefronts the local merge runs with where nobody chose a configuration (the
-// other phases and the workspace depend on the tile height alone): 8 for
-// 32-row tiles, whose images leave the chip idle, so that the loops over a
-// tile's nodes take one pass (4-connectivity noise: 480 x 640 16.6 us a call
-// with 8, 17.3 with 4; 1080 x 1920 20.3 and 20.6; 8-connectivity 1080 x 1920
-// 25.3 and 25.1).
-inline int merge_waves(int th, int nw) { return th == 32 && nw == 4 ? 8 : nw; }
+// Wavefronts the local merge of one image runs with where nobody chose a
+// configuration (the other phases and the workspace depend on the tile height
+// alone): 8 for up to 512 32-row tiles under 4-connectivity, whose bands hold
+// twice the intervals, so that the loops over a tile's nodes take one pass while
+// wavefront slots are idle.  us a call with 4 and with 8, noise p = 0.5: 480 x
+// 640 16.2 and 15.6, 720 x 1280 (460 tiles) 17.5 and 17.1, 1080 x 1920 (1020)
+// 19.8 and 19.7, where smoothed fields take 21.9 and 22.3; 1200 x 2000 (1216
+// tiles, more than the chip's slots hold at once with 8) 21.1 and 22.7.  Under
+// 8-connectivity 8 is never faster: 480 x 640 18.9 both, 1200 x 2000 25.5 and 28.1.
+inline int merge_waves(const ImgView &v, int th, int nw, int conn) {
+    return th == 32 && nw == 4 && conn == 4 && (int64_t)v.tilesX * v.tilesY <= 512 ? 8 : nw;
+}
 // The kernels' view of one image whose workspace (ws_layout(H, W, th,
 // equal).total bytes, 256-byte aligned) starts at ws.
 ImgView make_view(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, uint32_t *labels,

@@ -68,7 +68,7 @@ extern "C" int ccl_label_2d_noalloc(const uint8_t *img, int32_t H, int32_t W, in
     // every workspace word the later phases read is written by the local
     // merge of the same call, so nothing is cleared here
     const ImgView v = make_view(img, H, W, pitch, labels, ws, th);
-    const hipError_t e = launch_plain(v, th, builtin ? merge_waves(th, nw) : nw, connectivity, (hipStream_t)stream);
+    const hipError_t e = launch_plain(v, th, builtin ? merge_waves(v, th, nw, connectivity) : nw, connectivity, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e);
     return CCL_OK;
 }

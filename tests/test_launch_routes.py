@@ -80,7 +80,7 @@ def test_tuning_leaves_small_images_in_one_launch(tmp_path):
     assert [len(res[i][1]) for i in (0, 2, 3, 7)] == [1, 1, 1, 1]
     assert res[4][1][0][0] == "k1_local_merge<64, 2, true, false>"
     assert len(res[5][1]) == 3
-    assert len(res[8][1]) == 3 and res[8][1][0][0] != "k1_local_merge<32, 8, true, false>"
+    assert len(res[8][1]) == 3 and res[8][1][0][0] != "k1_local_merge<32, 4, true, false>"
 
 
 def test_timed_call_launches_what_the_plain_call_does(tmp_path):
@@ -92,3 +92,16 @@ def test_timed_call_launches_what_the_plain_call_does(tmp_path):
     _accepted(res)
     for k in range(0, len(res), 2):
         assert res[k] == res[k + 1], calls[k]
+
+
+@pytest.mark.parametrize("fn", ["ex", "noalloc", "timed"])
+def test_wavefronts_of_the_merge(tmp_path, fn):
+    # 8 on up to 512 tiles of 32 rows under 4-connectivity, else 4
+    sizes = [(480, 640, 4, 512), (512, 2048, 4, 512), (513, 2048, 4, 256), (852, 3840, 4, 256), (480, 640, 8, 256),
+             (852, 3840, 8, 256), (2160, 3840, 4, 256)]
+    call = {"ex": lambda h, w, c: _plain(h, w, c),
+            "noalloc": lambda h, w, c: ("ccl_label_2d_noalloc", [IMG, h, w, w, c, LABELS, None]),
+            "timed": lambda h, w, c: ("ccl_label_2d_timed", [IMG, h, w, w, c, LABELS, None, None, 0])}[fn]
+    res = record([call(h, w, c) for h, w, c, _ in sizes], tmp_path)
+    _accepted(res)
+    assert [ls[0][3] for _, ls in res] == [s[3] for s in sizes]
