@@ -52,7 +52,9 @@ __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, u
             const uint32_t x = wx * (uint32_t)kTileW + (uint32_t)lane;
             const bool in = w0 + (uint32_t)i < words && x < W;
             p[i] = y * W + x;
-            l[i] = in ? L[p[i]] : 0u;
+            // outside the image its own index, never a root's label (0 is one's
+            // where p + 1 wraps around, H * W being close to 2^32)
+            l[i] = in ? L[p[i]] : p[i];
             if (++wx == WW) {
                 wx = 0u;
                 ++y;
@@ -61,9 +63,7 @@ __global__ void __launch_bounds__(256) st_roots(const uint32_t *L, uint32_t W, u
         uint64_t mine = 0ull;  // lane i: word i's mask
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
-            // (a lane outside the image holds 0, and its p + 1 wraps to 0 where
-            // H * W is close to 2^32)
-            const uint64_t m = __ballot(l[i] != 0u && l[i] == p[i] + 1u);
+            const uint64_t m = __ballot(l[i] == p[i] + 1u);
             if (lane == i) mine = m;
             cnt += (uint32_t)__popcll(m);
         }
