@@ -102,8 +102,8 @@ int ccl_version(void);
  * own workspace to ccl_label_2d_ex.  Images of few lines (two rows of 64
  * columns: ceil(H/2) * ceil(W/64)) for which the caller names no tile
  * configuration are labeled in one launch that needs no workspace, whatever
- * the tuning table holds: at most 120 lines under 4-connectivity; 128 under
- * 8-connectivity, 192 from 48 rows up.
+ * the tuning table holds: at most 128 lines under 4-connectivity and 160 under
+ * 8-connectivity, from 48 rows up 160 and 224.
  * Returns CCL_OK or an error; on error nothing has been enqueued (except
  * CCL_ERR_HIP from a failed launch).
  */
@@ -220,9 +220,9 @@ int ccl_component_stats(const uint32_t *labels, int32_t H, int32_t W, ccl_compon
 
 /*
  * ccl_label_2d_stats -- ccl_label_2d and ccl_component_stats in one call:
- * the link phase (Sec. II-C) also accumulates each component's area,
- * bounding box and coordinate sums while it holds every pixel's final root,
- * so the labels are not read back.
+ * the local merge (Sec. II-A) also accumulates the area, bounding box and
+ * coordinate sums of every component inside its tile, which are then added up
+ * by final label, so the labels are not read back.
  * img, H, W, pitch, connectivity, labels   as for ccl_label_2d (binary).
  * out, capacity, n_out   as for ccl_component_stats: record k is the
  *           component with the k-th smallest label; the first `capacity`

@@ -207,7 +207,7 @@ int ccl_label_2d_ex(const uint8_t *img, int32_t H, int32_t W, int64_t pitch, int
     // small images that the caller chose no configuration for are labeled in
     // one launch, without a workspace.  The tuning table holds configurations of
     // the three launches, the fastest of which is seldom as fast (120 x 160
-    // noise 16 us a call, 10 in one launch)
+    // noise, 8-connectivity, 15.5 us a call, 12.4 in one launch)
     const bool chosen = cfg && (cfg->tile_h != 0 || cfg->waves != 0);
     if (!chosen && small_image(H, W, connectivity)) {
         const hipError_t e = launch_small(make_view(img, H, W, pitch, labels, nullptr, th), connectivity, s);

@@ -2,9 +2,10 @@
 //
 // Tile model.  A tile is 64 pixels wide -- one lane of a 64-wide wavefront
 // per column -- and TH rows tall (TH in {16, 32, 64, 128}).  A workgroup of NW
-// wavefronts owns one tile at a time; wavefront w owns rows [w*RPW,
-// (w+1)*RPW) with RPW = TH / NW.  A tile row is a 64-bit foreground mask, so
-// the paper's row scan plus row-column unification (Sec. II-A-2) collapses
+// wavefronts owns one tile at a time.  The local merge spreads a tile's bands,
+// parts of eight columns and nodes over all its threads; in the link wavefront
+// w owns rows [w*RPW, (w+1)*RPW) with RPW = TH / NW.  A tile row is a 64-bit
+// foreground mask, so the paper's row scan plus row-column unification (Sec. II-A-2) collapses
 // to mask arithmetic: binary labeling takes two rows at a time, and the
 // components of such a band are column intervals found from its two masks;
 // those intervals are the union-find nodes, joined with the intervals of the

@@ -35,8 +35,10 @@ namespace ccl {
 // Equal-value local merge (every value class labeled, Sec. II-A's
 // "same property" test): nodes are the runs of equal values of every row,
 // lines are rows, and touching pairs are those of equal value.  2160 x 3840
-// in six levels, 8-connectivity: 24 us; sweeping the rows of each wavefront
-// one after the other took 39.5.
+// in six levels, 8-connectivity: 20 us; sweeping the rows of each wavefront
+// one after the other took 39.5.  The sweep was faster where nearly every run is
+// hooked or joined: 4096 x 4096 columns, 4-connectivity, 41 us against 56, a
+// checkerboard under 8-connectivity 56 against 94.
 template <int TH>
 struct K1EqLds {
     // Room for every join: a run of m pixels touches at most (m + 3) / 2 runs of
@@ -411,11 +413,11 @@ __global__ void __launch_bounds__(NW * 64) k3_link(ImgView v) {
 // the whole image, whose lines are the 64-column words of its bands in raster
 // order, with joins between neighbouring words of a band; the labels are
 // written from LDS.  Such a call is bound by launches and by the latency of a
-// phase, not by work: 64 x 64 of noise takes 12 us in three launches and 6 so,
-// 120 x 160 19 and 15 where the columns are staggered, 13 and 10 in noise.
+// phase, not by work: 64 x 64 of noise, p = 0.5, takes 11.6 us in three launches
+// and 6.1 so, 120 x 160, 8-connectivity, 15.6 and 12.4.
 // small_image() holds where the line lies.
 template <bool CONN8>
-constexpr int kSmallLines = CONN8 ? 192 : 128;  // room for, a multiple of 64
+constexpr int kSmallLines = CONN8 ? 256 : 192;  // room for, a multiple of 64
 
 template <bool CONN8>
 struct SmallLds {
@@ -701,20 +703,22 @@ hipError_t launch_plain(const ImgView &v, int th, int nw, int conn, hipStream_t 
     return hipErrorInvalidValue;
 }
 
-// One launch where no image of the size measured slower in it than in three, be
-// it noise, stripes, a checkerboard or staggered columns (us a call; the three
-// launches with 4 wavefronts in the merge, which ran all sizes before):
-//   4-connectivity, a checkerboard (most nodes): 120 lines 8.8 against 9.4,
-//     128 lines of 4 rows 9.3 and 9.1, 128 x 256 (256 lines) 16.2 and 10.5;
-//   8-connectivity, at most one row of 32-row tiles (columns): 128 lines of 32
-//     rows 8.8 and 9.8, 160 lines 10.2 and 9.8, 8 x 4096 14.1 and 9.2;
-//   8-connectivity, more rows, where the three launches join tiles below each
-//     other (staggered columns): 192 lines of 48 rows 15.8 and 17.3, 160 x 160
-//     (240 lines) 18.9 both, 512 x 64 19.9 and 18.6.
+// One launch up to the lines where noise takes no longer in it than in three
+// and the worst pattern (a checkerboard under 4-connectivity, columns or staggered
+// columns under 8) at most 2 % longer than in the three launches that ran every
+// size before.  us a call, three launches and one:
+//   4-connectivity: 4 x 4096 (128 lines) checkerboard 9.3 and 9.2; 64 x 320 (160)
+//     checkerboard 10.7 and 10.8, noise 1.2 times as fast; 4 x 5120 (160)
+//     checkerboard 9.3 and 10.9; 128 x 256 (256) 10.5 and 16.2;
+//   8-connectivity, at most one row of 32-row tiles: 32 x 640 (160) columns 10.0
+//     and 10.2, noise 1.2 times as fast; 8 x 4096 (256) columns 9.2 and 14.1;
+//   8-connectivity, more rows, where three launches join tiles below each other:
+//     56 x 512 (224) staggered columns 17.4 and 17.7, noise 1.1 times as fast;
+//     512 x 64 (256) staggered columns 18.6 and 19.9.
 bool small_image(int H, int W, int conn) {
     const int64_t lines = ((int64_t)H + 1) / 2 * (((int64_t)W + kTileW - 1) / kTileW);
-    if (conn == 4) return lines <= 120;
-    return lines <= (H >= 48 ? 192 : 128);
+    if (conn == 4) return lines <= (H >= 48 ? 160 : 128);
+    return lines <= (H >= 48 ? 224 : 160);
 }
 
 hipError_t launch_small(const ImgView &v, int conn, hipStream_t s) {

@@ -188,10 +188,11 @@ __device__ __forceinline__ uint32_t record_of(uint32_t r, uint32_t W, uint32_t W
 // 80 scalar registers (eight wavefronts per SIMD), so that two workgroups
 // share a compute unit; with 112 one ran at a time.  Gathering a label over a
 // wavefront's strip makes its eight LDS additions once per strip instead of
-// once per row.  2160 x 3840 smoothed labels: 46 us before, 35 so.  Blocks of
-// 128 x 256 take 28 there and 15 to 30 % less on large images of large
-// components, but up to 7 % more where components are many and small
-// (4-connectivity, p = 0.3), with half as many workgroups to share them.
+// once per row.  2160 x 3840 smoothed labels: 40 to 52 us by the field drawn with
+// blocks of 64 x 256 that added run by run, 26 to 43 so.  Blocks of 128 x 256
+// took 15 to 30 % less on large images of large components, but up to 7 % more
+// where components are many and small (4-connectivity, p = 0.3), with half as
+// many workgroups to share them.
 constexpr int kAccWaves = 16, kAccStripRows = 16;
 constexpr int kAccCols = 2 * kTileW;
 constexpr int acc_rows(int waves) { return waves / 2 * kAccStripRows; }

@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 # the last three rows: the first and last sizes of one launch and of three
 SHAPES = [(120, 160), (128, 192), (192, 128), (129, 130), (128, 256), (512, 64), (127, 250),
-          (240, 64), (241, 64), (2, 7680), (2, 7681), (47, 320),
-          (256, 64), (257, 64), (32, 512), (32, 513), (2, 8192), (2, 8193),
-          (48, 512), (48, 513), (384, 64), (385, 64)]
+          (320, 64), (321, 64), (2, 8192), (2, 8193), (32, 512), (32, 513),
+          (32, 640), (32, 641), (2, 10240), (2, 10241), (46, 384), (46, 449),
+          (48, 576), (48, 577), (448, 64), (449, 64)]
 
 
 def _staggered(H, W, step=2):

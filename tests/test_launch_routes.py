@@ -58,10 +58,10 @@ def test_nothing_runs_when_a_launch_is_refused(tmp_path):
 @pytest.mark.parametrize("fn", ["ex", "noalloc"])
 def test_sizes_of_one_launch(tmp_path, fn):
     # (size, connectivity): one launch up to the line, three beyond it
-    one = [(1, 1, 4), (240, 64, 4), (2, 7680, 4), (48, 320, 4), (256, 64, 8), (32, 512, 8), (2, 8192, 8), (47, 320, 8),
-           (48, 512, 8), (120, 160, 8), (384, 64, 8), (383, 1, 8)]
-    three = [(241, 64, 4), (2, 7681, 4), (120, 160, 4), (511, 1, 4), (32, 513, 8), (46, 384, 8), (2, 8193, 8), (385, 64, 8),
-             (48, 513, 8), (160, 160, 8), (512, 64, 8)]
+    one = [(1, 1, 4), (320, 64, 4), (2, 8192, 4), (48, 384, 4), (319, 1, 4), (32, 512, 4), (320, 64, 8), (32, 640, 8),
+           (2, 10240, 8), (46, 384, 8), (48, 576, 8), (120, 160, 8), (448, 64, 8), (447, 1, 8)]
+    three = [(321, 64, 4), (2, 8193, 4), (120, 160, 4), (511, 1, 4), (32, 513, 4), (32, 641, 8), (46, 449, 8), (2, 10241, 8),
+             (449, 64, 8), (48, 577, 8), (160, 160, 8), (512, 64, 8)]
     calls = [_plain(*s) if fn == "ex" else ("ccl_label_2d_noalloc", [IMG, s[0], s[1], s[1], s[2], LABELS, None])
              for s in one + three]
     for size, (rc, ls) in zip(one + three, record(calls, tmp_path)):
