@@ -35,7 +35,7 @@ def test_small_blocks(shape, conn):
 
 
 def test_dense_small_image_is_spread():
-    # 3 times the time of an empty image when one workgroup added it all up
+    # 4.5 times the time of an empty image when one workgroup added it all up
     import torch
     from paper_1708_08180_amd import binding
 
@@ -59,4 +59,4 @@ def test_dense_small_image_is_spread():
 
     dense, empty = us(wl.bernoulli(128, 128, 0.5, 9101)), us(np.zeros((128, 128), np.uint8))
     say("128x128: noise %.1f us, empty %.1f" % (dense, empty))
-    assert dense < 2.5 * empty
+    assert dense < 3.0 * empty
